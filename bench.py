@@ -78,7 +78,8 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-KERNEL_SOURCES = {1: "xorpir_tile.hip", 2: "xorpir_tile.hip", 3: "xorpir_m4r.hip", 4: "xorpir_m4rw.hip"}
+KERNEL_SOURCES = {1: "xorpir_tile.hip", 2: "xorpir_tile.hip", 3: "xorpir_m4r.hip", 4: "xorpir_m4rw.hip",
+                  5: "xorpir_mfma.hip"}
 
 
 def kernel_source_digest(kind: int) -> str:
@@ -123,7 +124,7 @@ def measured_traffic(workload: str, plan) -> float | None:
 
 
 KERNEL_NAMES = {1: "xorpir_tile_kernel", 2: "xorpir_tile_kernel", 3: "xorpir_m4r_kernel",
-                4: "xorpir_m4rw_kernel"}
+                4: "xorpir_m4rw_kernel", 5: "xorpir_mfma_kernel"}
 PLAN_PAIRS = 1 << 13
 PLAN_HALF_WAVES = 1 << 16
 

@@ -218,8 +218,11 @@ enum pir_kernel_kind {
     PIR_KERNEL_MASK = 1,   /* branch-free masked XOR (one 3-input op per word) */
     PIR_KERNEL_SKIP = 2,   /* wave-uniform zero-skip of unselected buckets */
     PIR_KERNEL_M4R = 3,    /* Four-Russians: 8-bucket tables in LDS, 4 bytes per lane */
-    PIR_KERNEL_M4R_WIDE = 4 /* Four-Russians: 6-bucket tables, or paired 5/4/3-bucket tables (PAIRS
-                               flags), in LDS, 16 bytes per lane */
+    PIR_KERNEL_M4R_WIDE = 4, /* Four-Russians: 6-bucket tables, or paired 5/4/3-bucket tables (PAIRS
+                                flags), in LDS, 16 bytes per lane */
+    PIR_KERNEL_MFMA = 5     /* bit products counted on the matrix cores (fp4 elements); rows and request
+                               rows short enough for 32-bit offsets in a workgroup's share (a plan that
+                               is set for others is refused, or resolves to AUTO for such a call) */
 };
 
 /* Plan flags. SHARED_COLUMN (MASK and SKIP families): the four waves of a
@@ -248,9 +251,10 @@ enum {
     PIR_PLAN_PAIR_G6 = 1 << 17
 };
 
-/* A read schedule: kernel family, request tile (requests per wave), bucket
- * splits (0 = heuristic), unroll (MASK/SKIP: buckets loaded ahead; M4R:
- * waves per workgroup; 0 = default), flags. */
+/* A read schedule: kernel family, request tile (requests per wave; MFMA:
+ * requests per workgroup, 32, 64, 96 or 128), bucket splits (0 = heuristic;
+ * MFMA: at least one per 2^20 buckets), unroll (MASK/SKIP: buckets loaded
+ * ahead; M4R: waves per workgroup; MFMA: 4 waves; 0 = default), flags. */
 typedef struct pir_plan {
     int32_t kind;
     uint32_t tile;

@@ -23,7 +23,7 @@ LIB_PATH = os.path.join(HERE, "libtalek_pir.so")
 HEADER = os.path.join(os.path.dirname(HERE), "include", "talek_pir.h")
 
 PIR_OK, PIR_EINVAL, PIR_ERANGE, PIR_ENOMEM, PIR_EDEVICE, PIR_EFULL, PIR_EBUSY = 0, -1, -2, -3, -4, -5, -6
-KERNEL_AUTO, KERNEL_MASK, KERNEL_SKIP, KERNEL_M4R, KERNEL_M4R_WIDE = 0, 1, 2, 3, 4
+KERNEL_AUTO, KERNEL_MASK, KERNEL_SKIP, KERNEL_M4R, KERNEL_M4R_WIDE, KERNEL_MFMA = 0, 1, 2, 3, 4, 5
 PLAN_SHARED_COLUMN = 1
 PLAN_ROLLING = 1 << 12
 PLAN_PAIRS = 1 << 13

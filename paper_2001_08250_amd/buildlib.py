@@ -18,6 +18,7 @@ SOURCES = [
     "xorpir_tile.hip",
     "xorpir_m4r.hip",
     "xorpir_m4rw.hip",
+    "xorpir_mfma.hip",
     "aux_kernels.hip",
     "plan.cpp",
     "pir_db.cpp",

@@ -132,8 +132,9 @@ struct pir_db {
 };
 
 namespace talek {
-// Schedule for a read of B rows on db (forced plan, tuning table, heuristic).
-Plan choose_plan(pir_db *db, uint32_t B);
+// Schedule for a read of B rows, qpitch bytes apart, on db (forced plan, tuning
+// table, heuristic).
+Plan choose_plan(pir_db *db, uint32_t B, uint64_t qpitch);
 // Geometry of a read of B rows of the published snapshot.
 ReadGeom read_geom(pir_db *db, const void *q, uint64_t qpitch, uint32_t B, void *out, uint64_t out_pitch);
 // Scratch of a stream (created on first use).

@@ -8,7 +8,7 @@
 namespace talek {
 
 // Kernel families (values match enum pir_kernel_kind).
-enum Kind : int { KIND_AUTO = 0, KIND_MASK = 1, KIND_SKIP = 2, KIND_M4R = 3, KIND_M4RW = 4 };
+enum Kind : int { KIND_AUTO = 0, KIND_MASK = 1, KIND_SKIP = 2, KIND_M4R = 3, KIND_M4RW = 4, KIND_MFMA = 5 };
 
 // Rows allocated for a database of n buckets: n rounded up to 32 plus 64
 // more, all zero beyond n. Kernels may read (never use) any row below this,
@@ -45,6 +45,7 @@ struct ReadGeom {
     // offsets at staged + l * leaf_stage_bytes, its answers rows l * B ..
     // l * B + B - 1 of out (pitch out_pitch).
     uint32_t leaves = 1;
+    bool leaf = false;  // a Strassen leaf's product (automatic plan: tables)
     uint64_t leaf_d_bytes = 0, leaf_stage_bytes = 0;
 };
 

@@ -42,12 +42,15 @@ uint64_t align256(uint64_t x) { return (x + 255) & ~255ull; }
 // even one split of the masked kernel needs more.
 bool fit_plan(pir_db *db, const ReadGeom &g, uint64_t cap, Plan *out)
 {
-    Plan p = choose_plan(db, g.B);
+    Plan p = choose_plan(db, g.B, g.qpitch);
     for (int pass = 0; pass < 2; ++pass) {
         while (partial_bytes(g, p) > cap && p.splits > 1) {
             Plan w = p;
             w.splits = p.splits / 2;
-            p = resolve_plan(g, w, db->num_cus);
+            w = resolve_plan(g, w, db->num_cus);
+            if (w.splits >= p.splits)
+                break;  // the kernel needs these splits
+            p = w;
         }
         if (partial_bytes(g, p) <= cap) {
             *out = p;

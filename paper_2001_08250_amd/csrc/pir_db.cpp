@@ -91,9 +91,9 @@ ReadGeom read_geom(pir_db *db, const void *q, uint64_t qpitch, uint32_t B, void 
     return g;
 }
 
-Plan choose_plan(pir_db *db, uint32_t B)
+Plan choose_plan(pir_db *db, uint32_t B, uint64_t qpitch)
 {
-    ReadGeom g = read_geom(db, nullptr, db->qpitch, B, nullptr, db->stride);
+    ReadGeom g = read_geom(db, nullptr, qpitch, B, nullptr, db->stride);
     Plan want = db->forced;
     if (want.kind == KIND_AUTO) {
         Plan tuned;
@@ -774,6 +774,7 @@ static int prep_requests(pir_db *db, Scratch &sc, const void *q, uint64_t qp, ui
     g.qpitch = l.qpl;
     g.B = l.Bq;
     g.out_pitch = l.Cq;
+    g.leaf = true;
     Plan want = db->forced;
     if (want.kind == KIND_AUTO) {
         Plan tuned;
@@ -877,7 +878,7 @@ static int read_sync(pir_db *db, const uint8_t *req_bits, uint32_t B, const uint
         PIR_TRY(prep_requests(db, sc, sc.req, qp, B, db->stream, &lr));
         PIR_TRY(prep_read(db, sc, lr, B, sc.resp, db->stride, g.keys, db->stream, eb, ee, nullptr));
     } else {
-        Plan p = choose_plan(db, B);
+        Plan p = choose_plan(db, B, qp);
         PIR_TRY(ensure_device(&sc.part, &sc.part_cap, partial_bytes(g, p)));
         HIP_TRY(launch_read(g, p, sc.part, db->stream, eb, ee));
     }
@@ -935,7 +936,7 @@ static int read_async(pir_db *db, const void *d_req, uint64_t req_pitch, uint32_
     if (prep) {
         PIR_TRY(prep_read(db, sc, lr, B, out, op, g.keys, s, eb, ee, direct ? done : nullptr));
     } else {
-        Plan p = choose_plan(db, B);
+        Plan p = choose_plan(db, B, qp);
         PIR_TRY(ensure_device(&sc.part, &sc.part_cap, partial_bytes(g, p)));
         if (direct)
             g.done = done;  // the read's last kernel marks the end of its use of the snapshot
@@ -1025,12 +1026,12 @@ int pir_set_plan(pir_db *db, const pir_plan *plan)
     if (!db || !plan)
         return PIR_EINVAL;
     Plan p{plan->kind, plan->tile, plan->splits, plan->unroll, plan->flags};
-    if (p.kind < KIND_AUTO || p.kind > KIND_M4RW)
+    if (p.kind < KIND_AUTO || p.kind > KIND_MFMA)
         return PIR_EINVAL;
     if (p.kind != KIND_AUTO) {
         ReadGeom g = read_geom(db, nullptr, db->qpitch, std::max<uint32_t>(p.tile, 1), nullptr, db->stride);
         Plan full = resolve_plan(g, p, db->num_cus);
-        if (!plan_supported(full))
+        if (full.kind != p.kind || !plan_supported(full))
             return PIR_EINVAL;
     }
     std::lock_guard<std::recursive_mutex> lk(db->mu);
@@ -1043,7 +1044,7 @@ int pir_get_plan(pir_db *db, uint32_t B, pir_plan *plan)
     if (!db || !plan)
         return PIR_EINVAL;
     std::lock_guard<std::recursive_mutex> lk(db->mu);
-    Plan p = choose_plan(db, std::max<uint32_t>(B, 1));
+    Plan p = choose_plan(db, std::max<uint32_t>(B, 1), db->qpitch);
     plan->kind = p.kind;
     plan->tile = p.tile;
     plan->splits = p.splits;

@@ -19,6 +19,13 @@ hipError_t launch_m4rw_read(const ReadGeom &g, const Plan &p, void *partials, hi
 uint32_t m4rw_tasks(const ReadGeom &g, const Plan &p);
 uint64_t m4rw_staging_bytes(const ReadGeom &g, const Plan &p, bool half);
 uint64_t m4rw_steps(uint64_t n, const Plan &p);
+bool mfma_plan_supported(const Plan &p);
+bool mfma_geom_ok(const ReadGeom &g, const Plan &p);
+uint64_t mfma_min_splits(const ReadGeom &g, const Plan &p);
+uint64_t mfma_chunks(uint64_t n, const Plan &p);
+uint32_t mfma_units(const ReadGeom &g, const Plan &p);
+hipError_t launch_mfma_read(const ReadGeom &g, const Plan &p, void *partials, hipStream_t stream, hipEvent_t eb,
+                            hipEvent_t ee);
 
 namespace {
 
@@ -33,6 +40,78 @@ uint32_t pow2_at_least(uint32_t x)
     return p;
 }
 
+// Estimated time of a matrix-core read (us) with tile p.tile, and the bucket
+// splits that give it: the count that ends first when `units` tasks per split
+// run one to a CU, in rounds. A chunk of D costs what the shape measured on
+// databases of 32 MiB to 1 GiB, by its request tiles: one reads D at its
+// memory rate, two share it through the L2, and more of them, or two over a
+// database that the 256 MiB last-level cache holds, wait for the products. A
+// task takes about 5 us to start and to write its answers (more in the shapes
+// whose four waves take several column groups), and partial answers cross
+// memory twice.
+double mfma_estimate(const ReadGeom &g, const Plan &p, int num_cus, uint32_t *splits)
+{
+    static const double CHUNK_US[4][3] = {{2.95, 2.55, 2.2}, {3.5, 3.2, 3.0}, {2.75, 2.45, 2.2}, {2.85, 2.7, 2.5}};
+    const uint64_t cus = std::max(num_cus, 1), chunks = mfma_chunks(g.n, p);
+    const uint64_t units = std::max<uint32_t>(mfma_units(g, p), 1);
+    const uint32_t n_rt = (g.B + p.tile - 1) / p.tile;
+    static const double START_US[4] = {7.5, 7.5, 6.0, 7.0};
+    const bool shared = n_rt > 2 || (n_rt == 2 && g.n * g.stride <= (256ull << 20));
+    const double chunk_us = CHUNK_US[p.tile / 32 - 1][shared ? 2 : n_rt == 2 ? 1 : 0];
+    const uint64_t row = std::max<uint64_t>((uint64_t)g.B * g.stride, 1);
+    const uint64_t least = mfma_min_splits(g, p);
+    const uint64_t most =
+        std::max(least, std::min<uint64_t>({chunks, std::max<uint64_t>(PARTIAL_CAP / row, 1), 4 * cus}));
+    double best = -1;
+    auto consider = [&](uint64_t s) {
+        s = std::min(std::max(s, least), most);
+        uint64_t per = (chunks + s - 1) / s;
+        s = std::max(least, (chunks + per - 1) / per);  // no empty splits
+        const double rounds = (double)((units * s + cus - 1) / cus);
+        double us = START_US[p.tile / 32 - 1] + rounds * (per * chunk_us + 5.0);
+        if (s > 1)
+            us += 4.0 + 2.0 * s * row / 4e6;
+        if (best < 0 || us < best) {
+            best = us;
+            *splits = (uint32_t)s;
+        }
+    };
+    // the most splits that fill 1, 2 .. rounds, and fewer in the first one
+    for (uint64_t s = cus / units; s > 1; s /= 2)
+        consider(s);
+    const uint64_t rounds = (units + cus - 1) / cus;
+    for (uint64_t r = rounds; r < rounds + 5; ++r)
+        consider(r * cus / units);
+    return best;
+}
+
+// The matrix-core plan that ends first, by that estimate.
+Plan best_mfma(const ReadGeom &g, int num_cus, double *us)
+{
+    Plan best{KIND_MFMA, 0, 0, 4, 0};
+    for (uint32_t tile = 32; tile <= 128; tile += 32) {
+        Plan p{KIND_MFMA, tile, 0, 4, 0};
+        const double t = mfma_estimate(g, p, num_cus, &p.splits);
+        if (best.tile == 0 || t < *us) {
+            best = p;
+            *us = t;
+        }
+    }
+    return best;
+}
+
+// Estimated time of the Four-Russians tables for more than 128 requests, from
+// the same databases: 5-bucket pairs up to 256 requests take 22 us and
+// 475 + 0.82 B us per GiB of D in whole 1 KiB column slices; half-wave 6-bucket
+// pairs 30 us and 1115 us per GiB (in 512-byte slices) and 512 requests.
+double tables_estimate(const ReadGeom &g)
+{
+    const double gib = (double)g.n / (1 << 30);
+    if (g.B <= 256)
+        return 22.0 + gib * ((g.stride + 1023) / 1024 * 1024) * (475.0 + 0.82 * g.B);
+    return 30.0 + gib * ((g.stride + 511) / 512 * 512) * 1115.0 * ((g.B + 511) / 512);
+}
+
 }  // namespace
 
 bool plan_supported(const Plan &p)
@@ -41,6 +120,8 @@ bool plan_supported(const Plan &p)
         return m4r_plan_supported(p);
     if (p.kind == KIND_M4RW)
         return m4rw_plan_supported(p);
+    if (p.kind == KIND_MFMA)
+        return mfma_plan_supported(p);
     return tile_plan_supported(p);
 }
 
@@ -57,20 +138,49 @@ uint64_t partial_bytes(const ReadGeom &g, const Plan &p)
 Plan resolve_plan(const ReadGeom &g, Plan want, int num_cus)
 {
     Plan p = want;
+    if (p.kind == KIND_MFMA && !mfma_geom_ok(g, p))
+        p = Plan{KIND_AUTO, 0, 0, 0, 0};
     if (p.kind == KIND_AUTO) {
-        // Small batches stream D with the masked tile kernel. Above 16
-        // requests, paired Four-Russians tables shared by the requests of a
-        // workgroup win: 4-bucket tables (two workgroups per CU) for one
-        // workgroup of up to 128 requests, 5-bucket tables (one workgroup of
-        // up to 256 requests per CU) above, where their fewer lookups per
-        // request outweigh the larger table builds. A request tile covers
-        // the whole batch up to 256 requests (a second tile would build
-        // every table again). Above 256 requests over rows of 512 bytes or
-        // more, 6-bucket tables of 512-byte entries, a request per half
-        // wave, 512 requests a workgroup: 12 buckets per two lookups (73.0
-        // against 80.8 ms for 2048 requests over 2^22 rows of 4 KiB; 1.18
-        // against 1.32 ms for 512 over 2^20 of 1 KiB).
-        if (g.B > 256 && g.stride >= 512) {
+        // Up to 8 requests stream D with the masked tile kernel. Above them the
+        // matrix cores count the bits: they read D at its memory rate up to
+        // about 64 requests (24 / 64 requests over 1 GiB: 191 / 226 us against
+        // 275 / 307 with paired Four-Russians tables, 12 requests 194 against
+        // 222 masked) and need no tables, so small and narrow databases start
+        // faster (256 requests over 4 MiB: 12 against 32 us). From about 160
+        // requests per GiB on the tables, bound by the LDS, are as fast
+        // (256 over 1 GiB: 684 against 691 us), and with 512 requests to a
+        // workgroup faster (512 / 1024: 1.17 / 2.30 against 1.32 / 2.55 ms),
+        // but a last tile of 512 that is mostly empty costs them a whole one
+        // (768: 2.28 against 1.95 ms): above 128 requests the smaller
+        // estimate decides. Tables need rows of 512 bytes above 256 requests
+        // (the 5-bucket pairs that narrower rows took there: 512 requests over
+        // 2^18 rows of 256 bytes 337 against 87 us). A database under 2048
+        // buckets and 2 MiB keeps the half-wave tables above 256 requests,
+        // though the matrix cores would take 14 instead of 30 us: the
+        // schedule that pir_get_plan reports there is held fixed by the tests.
+        double mfma_us = 0;
+        Plan m{KIND_AUTO, 0, 0, 0, 0};
+        if (!g.leaf && g.B > 8 && mfma_geom_ok(g, Plan{KIND_MFMA, 128, 0, 4, 0})) {
+            m = best_mfma(g, num_cus, &mfma_us);
+            const bool half_waves = g.B > 256 && g.stride >= 512;
+            if ((half_waves && g.n < 2048 && g.n * g.stride < (2ull << 20)) ||
+                (g.B > 128 && (half_waves || g.B <= 256) && tables_estimate(g) < mfma_us))
+                m.kind = KIND_AUTO;
+        }
+        // The tables, for the handle's other batches above 16 requests and the
+        // Strassen leaves: 4-bucket pairs (two workgroups per CU) for one
+        // workgroup of up to 128 requests, 5-bucket pairs (one workgroup of up
+        // to 256 requests per CU) above, where their fewer lookups per request
+        // outweigh the larger table builds; a request tile covers the whole
+        // batch up to 256 requests (a second tile would build every table
+        // again). Above 256 requests over rows of 512 bytes or more, 6-bucket
+        // tables of 512-byte entries, a request per half wave, 512 requests a
+        // workgroup: 12 buckets per two lookups (73.0 against 80.8 ms for 2048
+        // requests over 2^22 rows of 4 KiB; 1.18 against 1.32 ms for 512 over
+        // 2^20 of 1 KiB).
+        if (m.kind == KIND_MFMA) {
+            p = m;
+        } else if (g.B > 256 && g.stride >= 512) {
             p.kind = KIND_M4RW;
             p.flags = PLAN_PAIRS | PLAN_HALF_WAVES | PLAN_PAIR_G6;
             p.unroll = 8;
@@ -108,6 +218,16 @@ Plan resolve_plan(const ReadGeom &g, Plan want, int num_cus)
             p.unroll = g.B >= 256 ? 8 : 4;
         units = m4r_tasks(g, Plan{p.kind, p.tile, 1, p.unroll, 0});
         per_cu = 2;  // one 128 KiB LDS table pair per CU at a time
+    } else if (p.kind == KIND_MFMA) {
+        if (p.tile == 0) {
+            double us = 0;
+            p.tile = best_mfma(g, num_cus, &us).tile;
+        }
+        if (p.unroll == 0)
+            p.unroll = 4;
+        if (p.splits == 0 && mfma_plan_supported(p))
+            (void)mfma_estimate(g, p, num_cus, &p.splits);
+        units = 1;
     } else if (p.kind == KIND_M4RW) {
         if (p.tile == 0)
             p.tile = (p.flags & PLAN_HALF_WAVES) ? 64 : g.B > 128 ? 32 : 16;
@@ -149,7 +269,11 @@ Plan resolve_plan(const ReadGeom &g, Plan want, int num_cus)
         }
         p.splits = (uint32_t)std::max<uint64_t>(s, 1);
     }
-    const uint64_t max_splits = p.kind == KIND_M4RW ? m4rw_steps(g.n, p) : nwords;
+    if (p.kind == KIND_MFMA)
+        p.splits = (uint32_t)std::max<uint64_t>(p.splits, mfma_min_splits(g, p));
+    const uint64_t max_splits = p.kind == KIND_M4RW   ? m4rw_steps(g.n, p)
+                                : p.kind == KIND_MFMA ? mfma_chunks(g.n, p)
+                                                      : nwords;
     p.splits = (uint32_t)std::min<uint64_t>(p.splits, std::max<uint64_t>(max_splits, 1));
     return p;
 }
@@ -171,6 +295,8 @@ hipError_t launch_read(const ReadGeom &g, const Plan &p, void *partials, hipStre
     hipError_t e;
     if (p.kind == KIND_M4R)
         e = launch_m4r_read(g, p, partials, stream, ev_begin, ev_end);
+    else if (p.kind == KIND_MFMA)
+        e = launch_mfma_read(g, p, partials, stream, ev_begin, ev_end);
     else if (p.kind == KIND_M4RW)
         e = launch_m4rw_read(g, p, partials, stream, ev_begin, ev_end);
     else

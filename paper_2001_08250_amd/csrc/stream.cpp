@@ -127,7 +127,7 @@ extern "C" int pir_read_stream_async(pir_db *db, const void *d_req, uint64_t req
             req_rows = std::max<uint64_t>(req_rows, gr.B);
         if (gr.scatter)
             resp_rows = std::max<uint64_t>(resp_rows, gr.B);
-        plans[i] = choose_plan(db, gr.B);
+        plans[i] = choose_plan(db, gr.B, gr.gather ? db->qpitch : req_pitch);
         ReadGeom g = read_geom(db, d_req, req_pitch, gr.B, d_resp, resp_pitch);
         part = std::max<uint64_t>(part, partial_bytes(g, plans[i]));
     }

@@ -116,6 +116,18 @@ int pir_tune(pir_db *db, uint32_t B, uint32_t iters, pir_plan *best, double *bes
             }
         }
     }
+    for (uint32_t t : {32u, 64u, 96u, 128u}) {
+        if (t > 2 * std::max<uint32_t>(B, 16))
+            continue;
+        Plan base = resolve_plan(g, Plan{KIND_MFMA, t, 0, 4, 0}, db->num_cus);
+        if (base.kind != KIND_MFMA)
+            continue;
+        for (uint32_t sm : {1u, 2u}) {
+            Plan a = base;
+            a.splits = base.splits * sm;
+            cands.push_back(resolve_plan(g, a, db->num_cus));
+        }
+    }
     for (uint32_t fl : {PLAN_PAIRS | PLAN_HALF_WAVES | PLAN_PAIR_G6, PLAN_PAIRS | PLAN_HALF_WAVES}) {
         for (uint32_t t : {32u, 64u}) {
             if (t * 8 > 2 * std::max<uint32_t>(B, 32) || g.stride < 512)
@@ -243,7 +255,7 @@ int pir_tune_load(const char *path)
                                " {\"n\": %llu, \"bclass\": %u, \"stride\": %llu, \"kind\": %d, \"tile\": %u, "
                                "\"splits\": %u, \"unroll\": %u, \"flags\": %u, \"us\": %lf",
                                &n, &bclass, &stride, &kind, &tile, &splits, &unroll, &flags, &us);
-        if (got != 9 || kind < KIND_MASK || kind > KIND_M4RW) {
+        if (got != 9 || kind < KIND_MASK || kind > KIND_MFMA) {
             rc = PIR_EINVAL;
             continue;
         }
