@@ -44,8 +44,8 @@ uint32_t pow2_at_least(uint32_t x)
 // splits that give it: the count that ends first when `units` tasks per split
 // run one to a CU, in rounds. A chunk of D costs what the shape measured on
 // databases of 32 MiB to 1 GiB, by its request tiles: one reads D at its
-// memory rate, two share it through the L2, and more of them, or two over a
-// database that the 256 MiB last-level cache holds, wait for the products. A
+// memory rate, two share it through the L2, and more of them, or any over a
+// database that the last-level cache holds, wait for the products. A
 // task takes about 5 us to start and to write its answers (more in the shapes
 // whose four waves take several column groups), and partial answers cross
 // memory twice.
@@ -56,7 +56,7 @@ double mfma_estimate(const ReadGeom &g, const Plan &p, int num_cus, uint32_t *sp
     const uint64_t units = std::max<uint32_t>(mfma_units(g, p), 1);
     const uint32_t n_rt = (g.B + p.tile - 1) / p.tile;
     static const double START_US[4] = {7.5, 7.5, 6.0, 7.0};
-    const bool shared = n_rt > 2 || (n_rt == 2 && g.n * g.stride <= (256ull << 20));
+    const bool shared = n_rt > 2 || g.n * g.stride <= CACHED_BYTES;
     const double chunk_us = CHUNK_US[p.tile / 32 - 1][shared ? 2 : n_rt == 2 ? 1 : 0];
     const uint64_t row = std::max<uint64_t>((uint64_t)g.B * g.stride, 1);
     const uint64_t least = mfma_min_splits(g, p);
@@ -141,7 +141,13 @@ Plan resolve_plan(const ReadGeom &g, Plan want, int num_cus)
     if (p.kind == KIND_MFMA && !mfma_geom_ok(g, p))
         p = Plan{KIND_AUTO, 0, 0, 0, 0};
     if (p.kind == KIND_AUTO) {
-        // Up to 8 requests stream D with the masked tile kernel. Above them the
+        // Up to 8 requests stream D with the masked tile kernel, except over
+        // rows so narrow that most lanes of its waves, 16 bytes each, have none:
+        // the matrix cores take 64 bytes of a row at least (one request over
+        // 256 MiB of 64-byte rows 74 against 141 us, 8 requests 78 against
+        // 442, over 64 MiB of 256-byte rows 23 against 30; level for up to 4
+        // requests over 256 MiB of 256-byte rows, for 8 over 32 MiB of
+        // 512-byte rows, and for one over 16 MiB of 64-byte rows). Above 8 the
         // matrix cores count the bits: they read D at its memory rate up to
         // about 64 requests (24 / 64 requests over 1 GiB: 191 / 226 us against
         // 275 / 307 with paired Four-Russians tables, 12 requests 194 against
@@ -160,7 +166,10 @@ Plan resolve_plan(const ReadGeom &g, Plan want, int num_cus)
         // schedule that pir_get_plan reports there is held fixed by the tests.
         double mfma_us = 0;
         Plan m{KIND_AUTO, 0, 0, 0, 0};
-        if (!g.leaf && g.B > 8 && mfma_geom_ok(g, Plan{KIND_MFMA, 128, 0, 4, 0})) {
+        const uint64_t bytes = g.n * g.stride;
+        const uint64_t narrow = g.B > 4 ? (bytes > (64ull << 20) ? 512 : 256) : bytes >= CACHED_BYTES ? 256 : 128;
+        const bool few = g.B <= 8 && !(bytes >= (16ull << 20) && g.stride <= narrow);
+        if (!g.leaf && !few && mfma_geom_ok(g, Plan{KIND_MFMA, 128, 0, 4, 0})) {
             m = best_mfma(g, num_cus, &mfma_us);
             const bool half_waves = g.B > 256 && g.stride >= 512;
             if ((half_waves && g.n < 2048 && g.n * g.stride < (2ull << 20)) ||
@@ -196,12 +205,30 @@ Plan resolve_plan(const ReadGeom &g, Plan want, int num_cus)
             p.unroll = 8;
             p.tile = g.B > 64 ? 16 : g.B > 32 ? 8 : 4;
         } else {
-            // masked XOR; from 4 to 8 requests the four waves of a workgroup
-            // share one 1 KiB column chunk (one wave's tile holds them all),
-            // which streams D faster than four chunks per workgroup
+            // Masked XOR. A database that the caches hold (up to 64 MiB) is
+            // read by as many waves as there are; from 5 to 8 requests two
+            // waves of 4 share a 1 KiB column chunk, which halves the chain
+            // of scalar work per bucket (8 requests over 4 MiB 11.3 us, one
+            // wave's tile of 8 13.3, over 64 MiB 19.7 and 20.5). A larger one
+            // streams best from few places at a time: four waves per CU, each
+            // 8 buckets ahead, take 158 us for one request over 1 GiB where
+            // 32 took 203 and 8 161 (8 requests 162, 8 waves of half the
+            // depth 171; over 256 MiB 48 and 54). Rows of several chunks
+            // that end in a fraction of one count as that fraction, rows of
+            // 512 bytes and less as half a chunk (4 requests over 256 MiB of
+            // 512-byte rows 51 against 53 us, of 256-byte rows 58 against 86).
             p.kind = KIND_MASK;
-            if (g.B >= 4 && g.B <= 8) {
+            if (bytes > (64ull << 20)) {
+                p.tile = pow2_at_least(std::max<uint32_t>(g.B, 1));
+                p.unroll = 8;
+                const uint64_t waves = 4ull * std::max(num_cus, 1);
+                uint64_t s = std::max<uint64_t>(waves * 64 / std::max<uint64_t>(g.stride / 16, 32), 1);
+                s = std::min<uint64_t>(s, std::max<uint64_t>(PARTIAL_CAP / (std::max(g.B, 1u) * g.stride), 1));
+                const uint64_t words = (g.n + 31) / 32, per = (words + s - 1) / s;
+                p.splits = (uint32_t)std::max<uint64_t>((words + per - 1) / per, 1);
+            } else if (g.B > 4) {
                 p.flags = PLAN_SHARED_COLUMN;
+                p.tile = 4;
                 p.unroll = 4;
             }
         }

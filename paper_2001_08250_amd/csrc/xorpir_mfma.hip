@@ -129,7 +129,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t chunk_of(const MfmaArgs &g, ui
 // A thread's share of a chunk: four columns of a quarter of the buckets of one
 // block, in G groups: row j of group e is bucket 4j + i, i = i0 + 2e (off: the
 // place of bucket i0). Blocks past the database read zero; their request bits
-// are zero too. ONCE: no other workgroup reads these rows.
+// are zero too. ONCE: no other workgroup reads these rows and no cache keeps
+// them for the next read.
 template <bool ONCE>
 __device__ __forceinline__ u32x4 load_row(__amdgpu_buffer_rsrc_t rows, uint32_t off, uint32_t at)
 {
@@ -501,7 +502,7 @@ using MfmaFn = void (*)(const MfmaArgs);
 
 // Shapes by requests per workgroup (the plan's tile).
 struct MfmaShape {
-    MfmaFn fn[2];      // D read by several request tiles, by one
+    MfmaFn fn[2];      // D read by several request tiles or kept by the cache; read once
     uint32_t cw, blk;  // 4-byte columns, 32-bucket blocks per chunk
 };
 
@@ -605,7 +606,7 @@ hipError_t launch_mfma_read(const ReadGeom &g, const Plan &p, void *partials, hi
         return hipErrorInvalidValue;
     a.tasks = (uint32_t)tasks;
     a.tasks_per_xcd = (uint32_t)((tasks + 7) / 8);
-    hipExtLaunchKernelGGL(s.fn[a.n_rt == 1], dim3(a.tasks_per_xcd * 8), dim3(THREADS), 0, stream, eb, ee, 0, a);
+    hipExtLaunchKernelGGL(s.fn[a.n_rt == 1 && g.n * g.stride > CACHED_BYTES], dim3(a.tasks_per_xcd * 8), dim3(THREADS), 0, stream, eb, ee, 0, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.splits <= 1)
         return e;

@@ -25,6 +25,13 @@
 //    with request tiles fastest. The request tiles that share a (split,
 //    column group) slice of D then run together on one XCD and reuse it from
 //    that XCD's L2.
+//
+// What bounds it. Up to 8 requests the stream of D: few deep streams keep the
+// memory rows open, so a large database is read by four waves per CU with 8
+// rows each in flight and, where no cache keeps it, by nontemporal loads (one
+// request over 1 GiB 158 us, 6.8 TB/s, 8 requests 161; 32 waves per CU with
+// plain loads 202, 8 waves 194). Small databases take two launches' time
+// (8 requests over 4 MiB 11.5 us).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -79,6 +86,19 @@ __device__ __forceinline__ void apply_bucket(uint4 (&acc)[T], const uint4 v, con
     }
 }
 
+// 16 bytes of D; ONCE: no other request tile reads them and no cache keeps them
+// for the next read.
+template <bool ONCE>
+__device__ __forceinline__ uint4 load_d(const uint8_t *p)
+{
+    using u32x4 = uint32_t __attribute__((ext_vector_type(4)));
+    if constexpr (ONCE) {
+        const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+        return make_uint4(v[0], v[1], v[2], v[3]);
+    }
+    return *reinterpret_cast<const uint4 *>(p);
+}
+
 // Accumulate buckets [jb, je) (jb a multiple of 32) of column `colc` for the
 // T request rows starting at r0 into acc. Rows >= B contribute nothing. One
 // loop iteration consumes one 32-bit request word; its 32 buckets are fully
@@ -90,7 +110,7 @@ __device__ __forceinline__ void apply_bucket(uint4 (&acc)[T], const uint4 v, con
 // zero). The row address is wave-uniform (SGPRs, advanced by the stride)
 // and the lane adds a fixed byte offset, so each load is one
 // global_load_dwordx4 with saddr + voffset.
-template <int T, int KIND, int U>
+template <int T, int KIND, int U, bool ONCE>
 __device__ __forceinline__ void tile_accumulate(uint4 (&acc)[T], const uint4 *__restrict__ D, uint32_t stride16,
                                                 uint64_t n, const uint32_t *__restrict__ Q, uint64_t qpitch_w,
                                                 uint32_t B, uint32_t r0, uint32_t colc, uint64_t jb, uint64_t je)
@@ -107,7 +127,7 @@ __device__ __forceinline__ void tile_accumulate(uint4 (&acc)[T], const uint4 *__
     uint4 nxt[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        nxt[u] = *reinterpret_cast<const uint4 *>(row + lane_off);
+        nxt[u] = load_d<ONCE>(row + lane_off);
         row += row_bytes;
     }
 
@@ -128,7 +148,7 @@ __device__ __forceinline__ void tile_accumulate(uint4 (&acc)[T], const uint4 *__
                 cur[u] = nxt[u];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                nxt[u] = *reinterpret_cast<const uint4 *>(row + lane_off);
+                nxt[u] = load_d<ONCE>(row + lane_off);
                 row += row_bytes;
             }
 #pragma unroll
@@ -143,7 +163,7 @@ __device__ __forceinline__ void tile_accumulate(uint4 (&acc)[T], const uint4 *__
 // SHARE = true: the 4 waves stream the same 1 KiB column chunk and take 4
 // consecutive request tiles, so the chunk is fetched from L2 once and the
 // other three waves hit in L1.
-template <int T, int KIND, int U, bool SHARE>
+template <int T, int KIND, int U, bool SHARE, bool ONCE>
 __global__ __launch_bounds__(WG) void xorpir_tile_kernel(const TileArgs a)
 {
     const uint32_t L = blockIdx.x;
@@ -172,7 +192,7 @@ __global__ __launch_bounds__(WG) void xorpir_tile_kernel(const TileArgs a)
     const uint64_t je = std::min<uint64_t>(a.n, we << 5);
 
     uint4 acc[T];
-    tile_accumulate<T, KIND, U>(acc, a.D, a.stride16, a.n, a.Q, a.qpitch_w, a.B, r0, colc, jb, je);
+    tile_accumulate<T, KIND, U, ONCE>(acc, a.D, a.stride16, a.n, a.Q, a.qpitch_w, a.B, r0, colc, jb, je);
 
     if (col_ok) {
         uint4 *o = a.out + (uint64_t)s * a.out_split16 + col;
@@ -235,45 +255,47 @@ __global__ __launch_bounds__(WG) void xor_splits_kernel(const uint4 *__restrict_
 
 using TileFn = void (*)(const TileArgs);
 
-template <int KIND, int U, bool SHARE>
+template <int KIND, int U, bool SHARE, bool ONCE>
 TileFn pick_tile(uint32_t T)
 {
     switch (T) {
-    case 1: return SHARE ? nullptr : xorpir_tile_kernel<1, KIND, U, false>;
-    case 2: return SHARE ? nullptr : xorpir_tile_kernel<2, KIND, U, false>;
-    case 4: return xorpir_tile_kernel<4, KIND, U, SHARE>;
-    case 8: return xorpir_tile_kernel<8, KIND, U, SHARE>;
-    case 16: return xorpir_tile_kernel<16, KIND, U, SHARE>;
-    case 24: return xorpir_tile_kernel<24, KIND, U, SHARE>;
-    case 32: return xorpir_tile_kernel<32, KIND, U, SHARE>;
+    case 1: return SHARE ? nullptr : xorpir_tile_kernel<1, KIND, U, false, ONCE>;
+    case 2: return SHARE ? nullptr : xorpir_tile_kernel<2, KIND, U, false, ONCE>;
+    case 4: return xorpir_tile_kernel<4, KIND, U, SHARE, ONCE>;
+    case 8: return xorpir_tile_kernel<8, KIND, U, SHARE, ONCE>;
+    case 16: return xorpir_tile_kernel<16, KIND, U, SHARE, ONCE>;
+    case 24: return xorpir_tile_kernel<24, KIND, U, SHARE, ONCE>;
+    case 32: return xorpir_tile_kernel<32, KIND, U, SHARE, ONCE>;
     default: return nullptr;
     }
 }
 
-template <int KIND>
+template <int KIND, bool ONCE>
 TileFn pick_tile_u(uint32_t T, uint32_t U, bool share)
 {
     switch (U) {
-    case 4: return share ? pick_tile<KIND, 4, true>(T) : pick_tile<KIND, 4, false>(T);
-    case 8: return share ? pick_tile<KIND, 8, true>(T) : pick_tile<KIND, 8, false>(T);
-    case 16: return share ? nullptr : pick_tile<KIND, 16, false>(T);
+    case 4: return share ? pick_tile<KIND, 4, true, ONCE>(T) : pick_tile<KIND, 4, false, ONCE>(T);
+    case 8: return share ? pick_tile<KIND, 8, true, ONCE>(T) : pick_tile<KIND, 8, false, ONCE>(T);
+    case 16: return share ? nullptr : pick_tile<KIND, 16, false, ONCE>(T);
     default: return nullptr;
     }
 }
 
-TileFn tile_fn(const Plan &p)
+TileFn tile_fn(const Plan &p, bool once)
 {
     const bool share = p.flags & PLAN_SHARED_COLUMN;
     if (p.kind == KIND_MASK)
-        return pick_tile_u<KIND_MASK>(p.tile, p.unroll, share);
+        return once ? pick_tile_u<KIND_MASK, true>(p.tile, p.unroll, share)
+                    : pick_tile_u<KIND_MASK, false>(p.tile, p.unroll, share);
     if (p.kind == KIND_SKIP)
-        return pick_tile_u<KIND_SKIP>(p.tile, p.unroll, share);
+        return once ? pick_tile_u<KIND_SKIP, true>(p.tile, p.unroll, share)
+                    : pick_tile_u<KIND_SKIP, false>(p.tile, p.unroll, share);
     return nullptr;
 }
 
 }  // namespace
 
-bool tile_plan_supported(const Plan &p) { return tile_fn(p) != nullptr; }
+bool tile_plan_supported(const Plan &p) { return tile_fn(p, false) != nullptr; }
 
 // Words per workgroup of the split reduction: all 256 threads on distinct
 // words while that gives at least 1024 workgroups (four per CU); fewer words
@@ -315,7 +337,11 @@ hipError_t launch_xor_splits(const void *partials, uint32_t splits, uint32_t B, 
 hipError_t launch_tile_read(const ReadGeom &g, const Plan &p, void *partials, hipStream_t stream, hipEvent_t eb,
                      hipEvent_t ee)
 {
-    TileFn fn = tile_fn(p);
+    const bool share = p.flags & PLAN_SHARED_COLUMN;
+    const uint32_t rows_per_wg = p.tile * (share ? 4u : 1u);
+    // shared columns: the workgroup's other tiles read them too, from its L1
+    const bool once = g.B <= p.tile && g.n * g.stride > CACHED_BYTES;
+    TileFn fn = tile_fn(p, once);
     if (!fn)
         return hipErrorInvalidValue;
     TileArgs a{};
@@ -325,8 +351,6 @@ hipError_t launch_tile_read(const ReadGeom &g, const Plan &p, void *partials, hi
     a.B = g.B;
     a.Q = static_cast<const uint32_t *>(g.Q);
     a.qpitch_w = g.qpitch / 4;
-    const bool share = p.flags & PLAN_SHARED_COLUMN;
-    const uint32_t rows_per_wg = p.tile * (share ? 4u : 1u);
     a.n_rt = (g.B + rows_per_wg - 1) / rows_per_wg;
     a.n_cg = share ? (a.stride16 + 63) / 64 : (a.stride16 + COLS_PER_WG - 1) / COLS_PER_WG;
     a.splits = p.splits;
