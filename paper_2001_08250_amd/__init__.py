@@ -394,10 +394,15 @@ class PirDB:
             call = lambda buf, cap: self._L.pir_interest_vector_encoded(self.h, buf, cap, ctypes.byref(size))
         else:
             call = lambda buf, cap: self._L.pir_interest_delta_encoded(self.h, epoch, buf, cap, ctypes.byref(size))
-        _check(call(None, 0), "interest_encoded (size)")
-        out = np.zeros(size.value, dtype=np.uint8)
-        _check(call(_ptr(out), out.size), "interest_encoded")
-        return out.tobytes()
+        # the header and the longest code of an m-bit vector, 3 m / 2 bits
+        m = getattr(self, "m_bits", IV_DEFAULT_BITS)
+        out = np.empty(24 + (m + m // 2) // 8 + 1, dtype=np.uint8)
+        rc = call(_ptr(out), out.size)
+        if size.value > out.size:  # a vector configured past this wrapper
+            out = np.empty(size.value, dtype=np.uint8)
+            rc = call(_ptr(out), out.size)
+        _check(rc, "interest_encoded")
+        return out[:size.value].tobytes()
 
     def interest_vector(self) -> np.ndarray:
         m = getattr(self, "m_bits", IV_DEFAULT_BITS)

@@ -59,20 +59,21 @@ __global__ __launch_bounds__(WG) void commit_kernel(const CommitArgs a)
             d[c] = s[c];
         return;
     }
-    constexpr uint32_t W = COMMIT_IV_WORDS, SL = WG / COMMIT_IV_WORDS;
-    __shared__ uint32_t part[SL][W];
+    constexpr uint32_t W = COMMIT_IV_WORDS, L = W / 4, SL = WG / L;
+    __shared__ uint4 part[SL][L];
     __shared__ uint32_t fresh[W];
-    const uint32_t lane = threadIdx.x % W, sl = threadIdx.x / W;
-    const uint64_t i = b * W + lane;
+    const uint32_t lane = threadIdx.x % L, sl = threadIdx.x / L;
+    const uint64_t words4 = a.words / 4, i = b * L + lane;
+    uint4 *ring = reinterpret_cast<uint4 *>(a.ring);
     if (threadIdx.x < W)
         fresh[threadIdx.x] = 0u;
-    uint32_t v = 0;
-    if (i < a.words) {
+    uint4 v = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll 8
-        for (uint32_t r = sl; r < a.window; r += SL)
-            if (r != a.slot)
-                v |= a.ring[(uint64_t)r * a.words + i];
-    }
+    for (uint32_t r = sl; r < a.window; r += SL)
+        if (r != a.slot) {
+            const uint4 x = ring[(uint64_t)r * words4 + i];
+            v = make_uint4(v.x | x.x, v.y | x.y, v.z | x.z, v.w | x.w);
+        }
     part[sl][lane] = v;
     __syncthreads();
     for (uint32_t j = a.pos_start[b] + threadIdx.x; j < a.pos_start[b + 1]; j += WG) {
@@ -82,13 +83,17 @@ __global__ __launch_bounds__(WG) void commit_kernel(const CommitArgs a)
             atomicOr(&fresh[w], 1u << (p & 31u));
     }
     __syncthreads();
-    if (sl == 0 && i < a.words) {
-        uint32_t o = fresh[lane];
-        a.ring[(uint64_t)a.slot * a.words + i] = o;
+    if (sl == 0) {
+        uint4 o = make_uint4(fresh[4 * lane], fresh[4 * lane + 1], fresh[4 * lane + 2], fresh[4 * lane + 3]);
+        ring[(uint64_t)a.slot * words4 + i] = o;
 #pragma unroll
-        for (uint32_t k = 0; k < SL; ++k)
-            o |= part[k][lane];
-        a.global[i] = o;
+        for (uint32_t k = 0; k < SL; ++k) {
+            const uint4 x = part[k][lane];
+            o = make_uint4(o.x | x.x, o.y | x.y, o.z | x.z, o.w | x.w);
+        }
+        reinterpret_cast<uint4 *>(a.global)[i] = o;
+        if (a.global_front)
+            reinterpret_cast<uint4 *>(a.global_front)[i] = o;
     }
 }
 

@@ -41,6 +41,7 @@ int hip_status(hipError_t e);  // hipSuccess -> PIR_OK, else PIR_EDEVICE
 
 // Grow a device buffer to at least `bytes` (contents are not kept).
 int ensure_device(void **p, uint64_t *cap, uint64_t bytes);
+int host_mapped(uint64_t bytes, void **host, void **dev);  // host memory that the device reads and writes
 
 void destroy_stream_graph(Scratch &sc);
 
@@ -119,6 +120,7 @@ struct pir_db {
     // compressed interest vectors: device scratch of the encoder
     void *codec = nullptr, *codec2 = nullptr, *codec3 = nullptr;
     uint64_t codec_cap = 0, codec2_cap = 0, codec3_cap = 0;
+    void *codec_host = nullptr, *codec_map = nullptr;  // result, mapped host memory
     uint64_t mirror_idx_cap = 0;
     // preprocessed reads: the Strassen leaf databases of the published
     // snapshot, rebuilt by every commit that changes it

@@ -150,18 +150,20 @@ hipError_t launch_xor_combine(const CombineArgs &a, hipStream_t stream);
 // Epoch commit, device half (one launch): staged rows into the back copy and
 // the interest-vector update (see commit_kernel).
 // Interest-vector words per commit block: a block's 256 threads are 16
-// slices of the window, so each thread ORs about window / 16 ring rows, all
-// loads in flight at once.
-constexpr uint32_t COMMIT_IV_WORDS = 16;
+// slices of the window, so each thread ORs 16 bytes of about window / 16 ring
+// rows, all loads in flight at once. (A window of 100 vectors of 0.6 MB, in
+// 256-byte pieces; with 64-byte pieces, 4 bytes per thread, it took 36 us.)
+constexpr uint32_t COMMIT_IV_WORDS = 64;
 struct CommitArgs {
     uint4 *back;               // back copy
     const uint4 *rows;         // nrows staged rows (stride16 uint4 each), mapped host memory
     const uint64_t *idx;       // their bucket indices, mapped host memory
     uint64_t nrows, stride16;
     uint32_t *global;          // global vector to write (the back copy's)
+    uint32_t *global_front;    // another copy of it to write, or none
     uint32_t *ring;            // window x words deltas
     uint32_t window, slot;     // slot = this epoch's delta
-    uint64_t words, iv_blocks; // iv_blocks = ceil(words / COMMIT_IV_WORDS)
+    uint64_t words, iv_blocks; // iv_blocks = words / COMMIT_IV_WORDS
     const uint32_t *pos;       // positions sorted by block, mapped host memory
     const uint32_t *pos_start; // block b: pos[pos_start[b] .. pos_start[b + 1])
 };

@@ -7,107 +7,260 @@
 // starts at -1), each as floor(g / 2^k) one-bits, a zero-bit and the k low
 // bits of g least significant first; bits fill bytes LSB first.
 //
-// Device pipeline, for a vector of W words: per-word popcounts and highest
-// set bits; an exclusive sum gives every word's first code index and an
-// exclusive max-scan the position set just before the word; the code lengths
-// of all set bits, scanned, give their bit offsets; each set bit then ORs its
-// code into the zeroed body. Only the header is assembled on the host.
+// Device pipeline, over tiles of 1024 words, three launches: every tile's set
+// bits and its last one, from which the launch's last workgroup has c, k and
+// the position set just before each tile; every tile's code bits, from which
+// it has their offsets; and the codes, ORed into the zeroed body, whose start
+// it writes to mapped host memory. The host waits once.
+//
+// What bounds it: launches and waits, not the vector (0.6 MB at the 100K
+// messages' size). Library scans over single words and single codes took 11
+// launches and three waits, 125 us an encoding; this takes about 25.
 #include <hip/hip_runtime.h>
-#include <hipcub/device/device_scan.hpp>
 
 #include <algorithm>
-#include <vector>
+#include <cstring>
 
 #include "db.h"
 
 namespace talek {
 namespace {
 
-constexpr int WG = 256;
+constexpr uint32_t WG = 256;
+constexpr uint32_t PER = 4;           // words per thread
+constexpr uint32_t TILE = WG * PER;   // words per workgroup
+constexpr uint64_t DIRECT = 1 << 16;  // body bytes that come by mapped memory
 
-__device__ __forceinline__ uint32_t valid_bits(const uint32_t *words, uint64_t w, uint64_t m)
+// What the passes of one encoding share, in device memory.
+struct CodecState {
+    uint64_t c, bits;
+    uint32_t k;
+    uint32_t done;  // workgroups of the running pass that have finished
+};
+
+// The result, in mapped host memory: the body's first DIRECT bytes follow.
+struct CodecResult {
+    uint64_t c, bits, k, pad;
+};
+
+struct CodecArgs {
+    const uint32_t *words;
+    uint64_t W, m;
+    uint32_t tiles;
+    CodecState *st;
+    uint64_t *count;   // per tile: set bits, then the position (+ 1) set before it
+    uint64_t *length;  // per tile: its last position (+ 1), then its code bits, then their offset
+    uint32_t *body;
+    uint64_t body_words;
+    CodecResult *result;
+};
+
+// Inclusive scan of one value per thread; *total is the workgroup's.
+template <class Op>
+__device__ __forceinline__ uint64_t scan(uint64_t v, Op op, uint64_t *waves, uint64_t *total)
 {
-    uint32_t v = words[w];
-    const uint64_t lo = w * 32;
-    if (lo + 32 > m)
-        v &= (m > lo) ? ((1u << (m - lo)) - 1u) : 0u;
-    return v;
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint64_t u = __shfl_up(v, d);
+        if (lane >= (uint32_t)d)
+            v = op(u, v);
+    }
+    __syncthreads();  // the last scan's readers are done with `waves`
+    if (lane == 63)
+        waves[wave] = v;
+    __syncthreads();
+    uint64_t before = 0, all = 0;
+    for (uint32_t w = 0; w < WG / 64; ++w) {
+        if (w == wave)
+            before = all;
+        all = op(all, waves[w]);
+    }
+    *total = all;
+    return op(before, v);
 }
 
-__global__ __launch_bounds__(WG) void word_stats_kernel(const uint32_t *__restrict__ words, uint64_t W, uint64_t m,
-                                                        uint64_t *__restrict__ counts, int64_t *__restrict__ last)
+struct Sum {
+    __device__ __forceinline__ uint64_t operator()(uint64_t a, uint64_t b) const { return a + b; }
+};
+struct Max {
+    __device__ __forceinline__ uint64_t operator()(uint64_t a, uint64_t b) const { return a > b ? a : b; }
+};
+
+// The value of the thread before this one (v inclusive; 0 for the first).
+__device__ __forceinline__ uint64_t before(uint64_t v, uint64_t *all)
 {
-    const uint64_t w = (uint64_t)blockIdx.x * WG + threadIdx.x;
-    if (w >= W)
-        return;
-    const uint32_t v = valid_bits(words, w, m);
-    counts[w] = (uint64_t)__popc(v);
-    last[w] = v ? (int64_t)(w * 32 + 31 - __clz(v)) : -1;
+    __syncthreads();
+    all[threadIdx.x] = v;
+    __syncthreads();
+    return threadIdx.x ? all[threadIdx.x - 1] : 0;
 }
 
-// MODE 0: code lengths into len[i]; MODE 1: codes ORed into body at off[i].
-template <int MODE>
-__global__ __launch_bounds__(WG) void codes_kernel(const uint32_t *__restrict__ words, uint64_t W, uint64_t m,
-                                                   const uint64_t *__restrict__ base,
-                                                   const int64_t *__restrict__ prev_last, uint32_t k,
-                                                   uint64_t *__restrict__ len, const uint64_t *__restrict__ off,
-                                                   uint32_t *__restrict__ body)
+// Whether this is the pass's last workgroup; it sees what the others' first
+// threads stored, and every atomic. (One release a workgroup: a fence by every
+// thread, each a write-back of the L2, took 20 us a pass.)
+__device__ __forceinline__ bool last_workgroup(CodecState *st, uint32_t tiles)
 {
-    const uint64_t w = (uint64_t)blockIdx.x * WG + threadIdx.x;
-    if (w >= W)
-        return;
-    uint32_t v = valid_bits(words, w, m);
-    int64_t prev = prev_last[w];
-    uint64_t i = base[w];
-    while (v) {
-        const uint32_t b = __ffs(v) - 1;
-        v &= v - 1;
-        const int64_t p = (int64_t)(w * 32 + b);
-        const uint64_t g = (uint64_t)(p - prev - 1);
-        const uint64_t q = g >> k;
-        if constexpr (MODE == 0) {
-            len[i] = q + 1 + k;
-        } else {
-            uint64_t at = off[i];
-            // q one-bits
-            for (uint64_t end = at + q; at < end;) {
-                const uint32_t s = (uint32_t)(at & 31);
-                const uint64_t nb = std::min<uint64_t>(32 - s, end - at);
-                const uint32_t mask = (nb == 32 ? 0xffffffffu : ((1u << nb) - 1u)) << s;
-                atomicOr(body + (at >> 5), mask);
-                at += nb;
-            }
-            ++at;  // the zero-bit
-            // the k low bits of g, least significant first
-            uint64_t r = k ? (g & ((k >= 64 ? ~0ull : (1ull << k)) - 1ull)) : 0;
-            for (uint64_t end = at + k; at < end;) {
-                const uint32_t s = (uint32_t)(at & 31);
-                const uint64_t nb = std::min<uint64_t>(32 - s, end - at);
-                const uint32_t chunk = (uint32_t)(r & (nb == 32 ? 0xffffffffull : ((1ull << nb) - 1ull)));
-                if (chunk)
-                    atomicOr(body + (at >> 5), chunk << s);
-                r >>= nb;
-                at += nb;
-            }
-        }
-        prev = p;
-        ++i;
+    __shared__ bool last;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        last = __hip_atomic_fetch_add(&st->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == tiles - 1;
+        if (last)
+            st->done = 0;
+    }
+    __syncthreads();
+    if (last)
+        __threadfence();
+    return last;
+}
+
+// This thread's words, bits at and past m cleared.
+__device__ __forceinline__ void load_words(const CodecArgs &a, uint64_t w0, uint32_t (&v)[PER])
+{
+#pragma unroll
+    for (uint32_t j = 0; j < PER; ++j) {
+        const uint64_t w = w0 + j;
+        v[j] = w < a.W ? a.words[w] : 0u;
+        if (w < a.W && w * 32 + 32 > a.m)
+            v[j] &= (1u << (a.m - w * 32)) - 1u;
     }
 }
 
-struct MaxOp {
-    __host__ __device__ __forceinline__ int64_t operator()(int64_t a, int64_t b) const { return a > b ? a : b; }
-};
-
-uint32_t blocks(uint64_t n) { return (uint32_t)std::max<uint64_t>(1, (n + WG - 1) / WG); }
-
-uint32_t rice_k(uint64_t m, uint64_t c)
+// The highest position (+ 1) set in them, 0 for none.
+__device__ __forceinline__ uint64_t last_position(const uint32_t (&v)[PER], uint64_t w0)
 {
-    uint64_t mean = std::max<uint64_t>(1, m / (c + 1));
-    uint32_t k = 0;
-    while ((mean >> (k + 1)) != 0)
-        ++k;
-    return k;
+    uint64_t last = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < PER; ++j)
+        if (v[j])
+            last = (w0 + j) * 32 + 32 - __clz(v[j]);
+    return last;
+}
+
+// f(gap) for every set bit, `prev` the position (+ 1) set before them.
+template <class F>
+__device__ __forceinline__ void each_gap(const uint32_t (&v)[PER], uint64_t w0, uint64_t prev, F f)
+{
+    for (uint32_t j = 0; j < PER; ++j) {
+        uint32_t x = v[j];
+        while (x) {
+            const uint64_t p = (w0 + j) * 32 + (__ffs(x) - 1);
+            x &= x - 1;
+            f(p - prev);
+            prev = p + 1;
+        }
+    }
+}
+
+__global__ __launch_bounds__(WG) void codec_count_kernel(const CodecArgs a)
+{
+    __shared__ uint64_t waves[WG / 64];
+    const uint64_t w0 = (uint64_t)blockIdx.x * TILE + threadIdx.x * PER;
+    uint32_t v[PER];
+    load_words(a, w0, v);
+    uint64_t n = 0, sum, last;
+#pragma unroll
+    for (uint32_t j = 0; j < PER; ++j)
+        n += __popc(v[j]);
+    scan(n, Sum(), waves, &sum);
+    scan(last_position(v, w0), Max(), waves, &last);
+    if (threadIdx.x == 0) {
+        a.count[blockIdx.x] = sum;
+        a.length[blockIdx.x] = last;
+    }
+    for (uint64_t i = (uint64_t)blockIdx.x * WG + threadIdx.x; i < a.body_words; i += (uint64_t)gridDim.x * WG)
+        a.body[i] = 0u;
+    if (!last_workgroup(a.st, a.tiles))
+        return;
+    __shared__ uint64_t all[WG];
+    uint64_t c = 0, prev = 0;
+    for (uint32_t t0 = 0; t0 < a.tiles; t0 += WG) {
+        const uint32_t t = t0 + threadIdx.x;
+        const bool in = t < a.tiles;
+        scan(in ? a.count[t] : 0, Sum(), waves, &sum);
+        const uint64_t upto = scan(in ? a.length[t] : 0, Max(), waves, &last);
+        const uint64_t b = before(upto, all);
+        if (in)
+            a.count[t] = prev > b ? prev : b;
+        c += sum;
+        prev = prev > last ? prev : last;
+    }
+    if (threadIdx.x == 0) {
+        const uint64_t mean = a.m / (c + 1);
+        a.st->c = c;
+        a.st->k = mean > 1 ? 63 - __clzll((long long)mean) : 0;
+    }
+}
+
+__global__ __launch_bounds__(WG) void codec_length_kernel(const CodecArgs a)
+{
+    __shared__ uint64_t waves[WG / 64], all[WG];
+    const uint64_t w0 = (uint64_t)blockIdx.x * TILE + threadIdx.x * PER;
+    const uint32_t k = a.st->k;
+    uint32_t v[PER];
+    load_words(a, w0, v);
+    uint64_t sum, bits = 0;
+    const uint64_t prev = before(scan(last_position(v, w0), Max(), waves, &sum), all);
+    each_gap(v, w0, std::max<uint64_t>(prev, a.count[blockIdx.x]), [&](uint64_t g) { bits += (g >> k) + 1 + k; });
+    scan(bits, Sum(), waves, &sum);
+    if (threadIdx.x == 0)
+        a.length[blockIdx.x] = sum;
+    if (!last_workgroup(a.st, a.tiles))
+        return;
+    uint64_t at = 0;
+    for (uint32_t t0 = 0; t0 < a.tiles; t0 += WG) {
+        const uint32_t t = t0 + threadIdx.x;
+        const uint64_t own = t < a.tiles ? a.length[t] : 0;
+        const uint64_t upto = scan(own, Sum(), waves, &sum);
+        if (t < a.tiles)
+            a.length[t] = at + upto - own;
+        at += sum;
+    }
+    if (threadIdx.x == 0) {
+        a.st->bits = at;
+        a.result->c = a.st->c;
+        a.result->bits = at;
+        a.result->k = k;
+    }
+}
+
+// ORs the nb low bits of x (x = ~0: ones) into the body at bit `at`.
+__device__ __forceinline__ void put(uint32_t *body, uint64_t at, uint64_t nb, uint64_t x, bool ones)
+{
+    while (nb) {
+        const uint32_t s = (uint32_t)(at & 31), here = (uint32_t)std::min<uint64_t>(32 - s, nb);
+        const uint32_t part = (ones ? ~0u : (uint32_t)x) & (here == 32 ? ~0u : (1u << here) - 1u);
+        if (part)
+            atomicOr(body + (at >> 5), part << s);
+        x >>= here;
+        at += here;
+        nb -= here;
+    }
+}
+
+__global__ __launch_bounds__(WG) void codec_write_kernel(const CodecArgs a)
+{
+    __shared__ uint64_t waves[WG / 64], all[WG];
+    const uint64_t w0 = (uint64_t)blockIdx.x * TILE + threadIdx.x * PER;
+    const uint32_t k = a.st->k;
+    uint32_t v[PER];
+    load_words(a, w0, v);
+    uint64_t sum, bits = 0;
+    uint64_t prev = before(scan(last_position(v, w0), Max(), waves, &sum), all);
+    prev = std::max<uint64_t>(prev, a.count[blockIdx.x]);
+    each_gap(v, w0, prev, [&](uint64_t g) { bits += (g >> k) + 1 + k; });
+    uint64_t at = a.length[blockIdx.x] + scan(bits, Sum(), waves, &sum) - bits;
+    each_gap(v, w0, prev, [&](uint64_t g) {
+        const uint64_t q = g >> k;
+        put(a.body, at, q, 0, true);
+        put(a.body, at + q + 1, k, g, false);
+        at += q + 1 + k;
+    });
+    if (!last_workgroup(a.st, a.tiles))
+        return;
+    const uint64_t words = std::min<uint64_t>((a.st->bits + 31) / 32, DIRECT / 4);
+    uint32_t *to = reinterpret_cast<uint32_t *>(a.result + 1);
+    for (uint64_t i = threadIdx.x; i < words; i += WG)
+        to[i] = a.body[i];
 }
 
 }  // namespace
@@ -120,90 +273,51 @@ int encode_interest(pir_db *db, const uint32_t *words, uint64_t m, uint8_t *out,
     const uint64_t W = (m + 31) / 32;
     if (W == 0 || W > 0x7fffffffull)
         return PIR_EINVAL;
-    // scratch: counts, base (u64) and last, prev_last (i64), W each
-    const uint64_t arr = (W * 8 + 255) & ~255ull;
-    size_t t1 = 0, t2 = 0;
-    if (hipcub::DeviceScan::ExclusiveSum(nullptr, t1, (uint64_t *)nullptr, (uint64_t *)nullptr, (int)W, s) !=
-            hipSuccess ||
-        hipcub::DeviceScan::ExclusiveScan(nullptr, t2, (int64_t *)nullptr, (int64_t *)nullptr, MaxOp(), (int64_t)-1,
-                                          (int)W, s) != hipSuccess)
-        return PIR_EDEVICE;
-    const uint64_t tmp = (std::max<size_t>(t1, t2) + 255) & ~255ull;
-    int rc = ensure_device(&db->codec, &db->codec_cap, 4 * arr + tmp);
+    CodecArgs a{};
+    a.words = words;
+    a.W = W;
+    a.m = m;
+    a.tiles = (uint32_t)((W + TILE - 1) / TILE);
+    // The codes take at most 3 m / 2 bits: c (k + 1) + (m - c) / 2^k with
+    // c < m / 2^k for k > 0, and m for k = 0.
+    const uint64_t body_words = (m + m / 2 + 31) / 32 + 1;
+    if (!db->codec) {
+        int rc = ensure_device(&db->codec, &db->codec_cap, sizeof(CodecState));
+        if (rc == PIR_OK && launch_fill_zero(db->codec, sizeof(CodecState), s) != hipSuccess)
+            rc = PIR_EDEVICE;
+        if (rc == PIR_OK && !db->codec_host)
+            rc = host_mapped(sizeof(CodecResult) + DIRECT, &db->codec_host, &db->codec_map);
+        if (rc != PIR_OK) {
+            hipFree(db->codec);
+            db->codec = nullptr;
+            db->codec_cap = 0;
+            return rc;
+        }
+    }
+    int rc = ensure_device(&db->codec2, &db->codec2_cap, 2ull * a.tiles * 8);
     if (rc != PIR_OK)
         return rc;
-    uint8_t *sc = static_cast<uint8_t *>(db->codec);
-    uint64_t *counts = reinterpret_cast<uint64_t *>(sc);
-    uint64_t *base = reinterpret_cast<uint64_t *>(sc + arr);
-    int64_t *last = reinterpret_cast<int64_t *>(sc + 2 * arr);
-    int64_t *prev_last = reinterpret_cast<int64_t *>(sc + 3 * arr);
-    void *temp = sc + 4 * arr;
-    hipLaunchKernelGGL(word_stats_kernel, dim3(blocks(W)), dim3(WG), 0, s, words, W, m, counts, last);
-    if (hipGetLastError() != hipSuccess)
-        return PIR_EDEVICE;
-    size_t tb = tmp;
-    if (hipcub::DeviceScan::ExclusiveSum(temp, tb, counts, base, (int)W, s) != hipSuccess)
-        return PIR_EDEVICE;
-    tb = tmp;
-    if (hipcub::DeviceScan::ExclusiveScan(temp, tb, last, prev_last, MaxOp(), (int64_t)-1, (int)W, s) !=
-        hipSuccess)
-        return PIR_EDEVICE;
-    uint64_t tail[2] = {0, 0};
-    if (hipMemcpyAsync(&tail[0], base + (W - 1), 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipMemcpyAsync(&tail[1], counts + (W - 1), 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return PIR_EDEVICE;
-    const uint64_t c = tail[0] + tail[1];
-    if (c > 0x7fffffffull)  // the device scans count in int
-        return PIR_EINVAL;
-    const uint32_t k = rice_k(m, c);
-
-    uint64_t bits = 0;
-    std::vector<uint8_t> body_host;
-    if (c > 0) {
-        // per set bit: code length, then its bit offset
-        const uint64_t carr = (c * 8 + 255) & ~255ull;
-        size_t t3 = 0;
-        if (hipcub::DeviceScan::ExclusiveSum(nullptr, t3, (uint64_t *)nullptr, (uint64_t *)nullptr, (int)c, s) !=
-            hipSuccess)
-            return PIR_EDEVICE;
-        const uint64_t tmp3 = (t3 + 255) & ~255ull;
-        rc = ensure_device(&db->codec2, &db->codec2_cap, 2 * carr + tmp3);
+    a.st = static_cast<CodecState *>(db->codec);
+    a.count = static_cast<uint64_t *>(db->codec2);
+    a.length = a.count + a.tiles;
+    a.result = static_cast<CodecResult *>(db->codec_map);
+    if (out) {
+        rc = ensure_device(&db->codec3, &db->codec3_cap, body_words * 4);
         if (rc != PIR_OK)
             return rc;
-        uint8_t *sc2 = static_cast<uint8_t *>(db->codec2);
-        uint64_t *len = reinterpret_cast<uint64_t *>(sc2);
-        uint64_t *off = reinterpret_cast<uint64_t *>(sc2 + carr);
-        hipLaunchKernelGGL(codes_kernel<0>, dim3(blocks(W)), dim3(WG), 0, s, words, W, m, base, prev_last, k, len,
-                           (const uint64_t *)nullptr, (uint32_t *)nullptr);
-        if (hipGetLastError() != hipSuccess)
-            return PIR_EDEVICE;
-        tb = tmp3;
-        if (hipcub::DeviceScan::ExclusiveSum(sc2 + 2 * carr, tb, len, off, (int)c, s) != hipSuccess)
-            return PIR_EDEVICE;
-        uint64_t lt[2] = {0, 0};
-        if (hipMemcpyAsync(&lt[0], off + (c - 1), 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipMemcpyAsync(&lt[1], len + (c - 1), 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)
-            return PIR_EDEVICE;
-        bits = lt[0] + lt[1];
-        const uint64_t nwords = (bits + 31) / 32;
-        rc = ensure_device(&db->codec3, &db->codec3_cap, nwords * 4);
-        if (rc != PIR_OK)
-            return rc;
-        uint32_t *body = static_cast<uint32_t *>(db->codec3);
-        if (launch_fill_zero(body, nwords * 4, s) != hipSuccess)
-            return PIR_EDEVICE;
-        hipLaunchKernelGGL(codes_kernel<1>, dim3(blocks(W)), dim3(WG), 0, s, words, W, m, base, prev_last, k,
-                           (uint64_t *)nullptr, off, body);
-        if (hipGetLastError() != hipSuccess)
-            return PIR_EDEVICE;
-        body_host.resize((bits + 7) / 8);
-        if (hipMemcpyAsync(body_host.data(), body, body_host.size(), hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)
-            return PIR_EDEVICE;
+        a.body = static_cast<uint32_t *>(db->codec3);
+        a.body_words = body_words;
     }
-    const uint64_t total = 24 + (bits + 7) / 8;
+    hipLaunchKernelGGL(codec_count_kernel, dim3(a.tiles), dim3(WG), 0, s, a);
+    hipLaunchKernelGGL(codec_length_kernel, dim3(a.tiles), dim3(WG), 0, s, a);
+    if (out)
+        hipLaunchKernelGGL(codec_write_kernel, dim3(a.tiles), dim3(WG), 0, s, a);
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
+        return PIR_EDEVICE;
+    const CodecResult res = *static_cast<const CodecResult *>(db->codec_host);
+    if (res.c > 0x7fffffffull)  // the stream's documented limit
+        return PIR_EINVAL;
+    const uint64_t bytes = (res.bits + 7) / 8, total = 24 + bytes;
     if (out_bytes)
         *out_bytes = total;
     if (!out)
@@ -212,13 +326,19 @@ int encode_interest(pir_db *db, const uint32_t *words, uint64_t m, uint8_t *out,
         return PIR_EINVAL;
     for (int i = 0; i < 8; ++i) {
         out[i] = (uint8_t)(m >> (8 * i));
-        out[8 + i] = (uint8_t)(c >> (8 * i));
+        out[8 + i] = (uint8_t)(res.c >> (8 * i));
     }
     for (int i = 0; i < 4; ++i) {
-        out[16 + i] = (uint8_t)(k >> (8 * i));
+        out[16 + i] = (uint8_t)(res.k >> (8 * i));
         out[20 + i] = 0;
     }
-    std::copy(body_host.begin(), body_host.end(), out + 24);
+    const uint64_t direct = std::min(bytes, DIRECT);
+    std::memcpy(out + 24, static_cast<const CodecResult *>(db->codec_host) + 1, direct);
+    if (bytes > direct &&
+        (hipMemcpyAsync(out + 24 + direct, reinterpret_cast<const uint8_t *>(a.body) + direct, bytes - direct,
+                        hipMemcpyDeviceToHost, s) != hipSuccess ||
+         hipStreamSynchronize(s) != hipSuccess))
+        return PIR_EDEVICE;
     return PIR_OK;
 }
 

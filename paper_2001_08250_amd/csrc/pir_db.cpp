@@ -34,6 +34,24 @@ int ensure_device(void **p, uint64_t *cap, uint64_t bytes)
     return PIR_OK;
 }
 
+// Pinned host memory that kernels read in place: *host for the CPU, *dev
+// for kernels.
+int host_mapped(uint64_t bytes, void **host, void **dev)
+{
+    *host = *dev = nullptr;
+    if (hipHostMalloc(host, std::max<uint64_t>(bytes, 64), hipHostMallocMapped) != hipSuccess) {
+        (void)hipGetLastError();
+        *host = nullptr;
+        return PIR_ENOMEM;
+    }
+    if (hipHostGetDevicePointer(dev, *host, 0) != hipSuccess) {
+        hipHostFree(*host);
+        *host = nullptr;
+        return PIR_EDEVICE;
+    }
+    return PIR_OK;
+}
+
 Scratch &scratch_for(pir_db *db, hipStream_t s) { return db->scratch[s]; }
 
 void destroy_stream_graph(Scratch &sc)
@@ -143,24 +161,6 @@ int ensure_back(pir_db *db)
 
 enum { UP_STAGE = 0, UP_POS = 1, UP_MIRROR = 2 };
 
-// Pinned host memory that kernels read in place: *host for the CPU, *dev
-// for kernels.
-int host_mapped(uint64_t bytes, void **host, void **dev)
-{
-    *host = *dev = nullptr;
-    if (hipHostMalloc(host, std::max<uint64_t>(bytes, 64), hipHostMallocMapped) != hipSuccess) {
-        (void)hipGetLastError();
-        *host = nullptr;
-        return PIR_ENOMEM;
-    }
-    if (hipHostGetDevicePointer(dev, *host, 0) != hipSuccess) {
-        hipHostFree(*host);
-        *host = nullptr;
-        return PIR_EDEVICE;
-    }
-    return PIR_OK;
-}
-
 // Block until pinned upload buffer `which` is no longer read by a queued copy.
 int wait_upload(pir_db *db, int which)
 {
@@ -240,7 +240,8 @@ int interest_alloc(pir_db *db, uint64_t m_bits, uint32_t window)
     hipFree(db->iv_global[0]);
     hipFree(db->iv_global[1]);
     db->iv_ring = db->iv_global[0] = db->iv_global[1] = nullptr;
-    const uint64_t words = (m_bits + 31) / 32;
+    // whole commit blocks: rows of the ring start on 256 bytes
+    const uint64_t words = (m_bits + 32 * COMMIT_IV_WORDS - 1) / (32 * COMMIT_IV_WORDS) * COMMIT_IV_WORDS;
     void *p = nullptr;
     if (hipMalloc(&p, words * 4 * window) != hipSuccess)
         return PIR_ENOMEM;
@@ -301,6 +302,8 @@ void free_db(pir_db *db)
     hipFree(db->codec);
     hipFree(db->codec2);
     hipFree(db->codec3);
+    if (db->codec_host)
+        hipHostFree(db->codec_host);
     for (auto &ev : db->prof_ev) {
         hipEventDestroy(ev.first);
         hipEventDestroy(ev.second);
@@ -536,7 +539,7 @@ int pir_epoch_commit(pir_db *db, uint64_t *epoch_out)
     // by block of COMMIT_IV_WORDS words (counting sort), in mapped host memory.
     PIR_TRY(wait_upload(db, UP_POS));
     const uint64_t npos = db->pos_pending.size();
-    const uint64_t nb = (db->iv_words + COMMIT_IV_WORDS - 1) / COMMIT_IV_WORDS;
+    const uint64_t nb = db->iv_words / COMMIT_IV_WORDS;
     if (npos + nb + 1 > db->pos_host_cap) {
         if (db->pos_host)
             hipHostFree(db->pos_host);
@@ -560,6 +563,10 @@ int pir_epoch_commit(pir_db *db, uint64_t *epoch_out)
     // The back copy's vector may still be read by async readers of the
     // buffer it belonged to before the last swap.
     PIR_TRY(wait_readers(db, back, db->stream));
+    // nothing written: only the interest vector moves, in both copies
+    const bool stay = !changed && !db->have_back;
+    if (stay)
+        PIR_TRY(wait_readers(db, db->front, db->stream));
     CommitArgs ca{};
     ca.back = reinterpret_cast<uint4 *>(db->buf[back]);
     ca.rows = static_cast<const uint4 *>(db->stage_map);
@@ -567,6 +574,7 @@ int pir_epoch_commit(pir_db *db, uint64_t *epoch_out)
     ca.nrows = rows;
     ca.stride16 = db->stride / 16;
     ca.global = db->iv_global[back];
+    ca.global_front = stay ? db->iv_global[db->front] : nullptr;
     ca.ring = db->iv_ring;
     ca.window = db->window;
     ca.slot = (uint32_t)(db->epoch % db->window);
@@ -584,12 +592,7 @@ int pir_epoch_commit(pir_db *db, uint64_t *epoch_out)
     }
     db->pos_pending.clear();
 
-    if (!changed && !db->have_back) {
-        // nothing written: only the interest vector moves. Keep the
-        // snapshot where it is and copy the new vector into the front slot.
-        PIR_TRY(wait_readers(db, db->front, db->stream));
-        HIP_TRY(hipMemcpyAsync(db->iv_global[db->front], db->iv_global[back], db->iv_words * 4,
-                               hipMemcpyDeviceToDevice, db->stream));
+    if (stay) {
         HIP_TRY(hipEventRecord(db->published, db->stream));
         db->epoch++;
         if (epoch_out)
