@@ -80,6 +80,8 @@ uint64_t partial_bytes(const ReadGeom &g, const Plan &p);
 // Fill in a complete plan (tile, splits, unroll) for geometry g from a
 // partial request (kind may be AUTO; zero fields mean "choose").
 Plan resolve_plan(const ReadGeom &g, Plan want, int num_cus);
+// Bucket splits for one launch of `leaves` products of geometry g under plan p.
+uint32_t leaf_splits(const ReadGeom &g, const Plan &p, uint32_t leaves, int num_cus);
 
 // Is the (kind, tile, unroll) combination compiled in?
 bool plan_supported(const Plan &p);

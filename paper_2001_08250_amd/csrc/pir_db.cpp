@@ -788,10 +788,15 @@ static int prep_requests(pir_db *db, Scratch &sc, const void *q, uint64_t qp, ui
     lr->staged = leaf_staging_supported(g, lr->p, t.leaves) &&
                  m4rw_staging_bytes(g, lr->p, true) * t.leaves <= PREP_STAGE_MAX;
     lr->q_leaf = lr->staged ? m4rw_staging_bytes(g, lr->p, true) : l.q_leaf;
+    const uint32_t one_leaf = lr->p.splits;
+    if (lr->staged && want.splits == 0)
+        lr->p.splits = leaf_splits(g, lr->p, t.leaves, db->num_cus);
     // one launch for every leaf: the leaves' answers are consecutive row
     // blocks of Bq rows
     const uint64_t split_bytes = lr->p.splits <= 1 ? 0 : (uint64_t)lr->p.splits * l.Bq * l.Cq;
     lr->fused = lr->staged && split_bytes * t.leaves <= PREP_PARTIAL_MAX;
+    if (!lr->fused)
+        lr->p.splits = one_leaf;
     lr->o_leaf = lr->fused ? (uint64_t)l.Bq * l.Cq : l.o_leaf;
     PIR_TRY(ensure_device(&sc.leaf_q, &sc.leaf_q_cap, lr->q_leaf * t.leaves));
     PIR_TRY(ensure_device(&sc.leaf_out, &sc.leaf_out_cap, lr->o_leaf * t.leaves));

@@ -305,6 +305,33 @@ Plan resolve_plan(const ReadGeom &g, Plan want, int num_cus)
     return p;
 }
 
+// One launch holds the tasks of every leaf, so it fills the CUs with few
+// splits: the count, up to the one a single leaf would take, that ends first
+// when a step of a pair-table kernel takes about 1.65 us (341 steps of 1024
+// requests over 256 MiB 573 us), a task five steps' time to start and to write
+// its answers, and the partial answers cross memory twice. 2048 requests over
+// 2 GiB in 49 leaves of 4 tasks: 13 splits are 10 rounds of 256 workgroups
+// all but full; with the 64 of a single leaf 49 rounds took 7.35 ms and their
+// 3.3 GB of partial answers another 0.6.
+uint32_t leaf_splits(const ReadGeom &g, const Plan &p, uint32_t leaves, int num_cus)
+{
+    const uint64_t steps = m4rw_steps(g.n, p);
+    const uint64_t tasks = (uint64_t)m4rw_tasks(g, p) * leaves;
+    const uint64_t slots = std::max(num_cus, 1) * (((p.flags >> PLAN_PAIR_G_SHIFT) & 3u) ? 2ull : 1ull);
+    const double bytes = 2.0 * leaves * g.B * g.stride;
+    uint32_t best = p.splits;
+    double least = -1;
+    for (uint64_t s = 1; s <= p.splits; ++s) {
+        const double us = (double)((tasks * s + slots - 1) / slots) * (1.65 * ((steps + s - 1) / s) + 8.0) +
+                          (s > 1 ? 4.0 + s * bytes / 4e6 : 0.0);
+        if (least < 0 || us < least) {
+            least = us;
+            best = (uint32_t)s;
+        }
+    }
+    return best;
+}
+
 hipError_t launch_split_reduce(const void *partials, uint32_t splits, const ReadGeom &g, hipStream_t stream)
 {
     if (g.keys)
