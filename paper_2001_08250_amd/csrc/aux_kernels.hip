@@ -193,6 +193,34 @@ __global__ __launch_bounds__(WG) void move_rows_kernel(uint32_t *__restrict__ ds
         d[c] = s[c];
 }
 
+// Row blockIdx.y of dst = the bytes of a row of src at any alignment, a word
+// per thread, zero past the row.
+__global__ __launch_bounds__(WG) void restage_rows_kernel(uint32_t *__restrict__ dst, uint64_t dst_pitch_w,
+                                                          const uint8_t *__restrict__ src, uint64_t src_pitch,
+                                                          uint64_t bytes, uint64_t rows)
+{
+    const uint64_t w = (uint64_t)blockIdx.x * WG + threadIdx.x;
+    if (w >= dst_pitch_w)
+        return;
+    for (uint64_t r = blockIdx.y; r < rows; r += gridDim.y) {
+        const uint8_t *s = src + r * src_pitch + w * 4;
+        uint32_t v = 0;
+        if (w * 4 + 4 <= bytes)
+            __builtin_memcpy(&v, s, 4);
+        else
+            for (uint32_t k = 0; w * 4 + k < bytes; ++k)
+                v |= (uint32_t)s[k] << (8 * k);
+        dst[r * dst_pitch_w + w] = v;
+    }
+}
+
+__global__ __launch_bounds__(WG) void fetch_kernel(uint4 *__restrict__ dst, const uint4 *__restrict__ src, uint64_t n)
+{
+    const uint64_t i = (uint64_t)blockIdx.x * WG + threadIdx.x;
+    if (i < n)
+        dst[i] = src[i];
+}
+
 uint32_t grid_for(uint64_t items)
 {
     uint64_t g = (items + WG - 1) / WG;
@@ -202,6 +230,32 @@ uint32_t grid_for(uint64_t items)
 }
 
 }  // namespace
+
+hipError_t launch_restage_rows(void *dst, uint64_t dst_pitch, const void *src, uint64_t src_pitch, uint64_t bytes,
+                               uint64_t rows, hipStream_t stream)
+{
+    const uint64_t x = (dst_pitch / 4 + WG - 1) / WG;
+    if (rows == 0 || x == 0)
+        return hipSuccess;
+    if (x * WG > 0xffffffffull)  // a grid dimension holds fewer than 2^32 work-items
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(restage_rows_kernel, dim3((uint32_t)x, (uint32_t)std::min<uint64_t>(rows, 65535)), dim3(WG), 0,
+                       stream, static_cast<uint32_t *>(dst), dst_pitch / 4, static_cast<const uint8_t *>(src),
+                       src_pitch, bytes, rows);
+    return hipGetLastError();
+}
+
+hipError_t launch_fetch(void *dst, const void *src, uint64_t bytes, hipStream_t stream)
+{
+    const uint64_t n = bytes / 16;
+    if (n == 0)
+        return hipSuccess;
+    if (bytes % 16 || n > 0xffffffffull - WG)
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(fetch_kernel, dim3((uint32_t)((n + WG - 1) / WG)), dim3(WG), 0, stream,
+                       static_cast<uint4 *>(dst), static_cast<const uint4 *>(src), n);
+    return hipGetLastError();
+}
 
 hipError_t launch_move_rows(void *dst, uint64_t dst_pitch, const uint64_t *dst_rows, const void *src,
                             uint64_t src_pitch, const uint64_t *src_rows, uint64_t count, uint64_t row_bytes,

@@ -29,6 +29,7 @@ struct Scratch {
     uint64_t keys_cap = 0;
     void *host_rows = nullptr;  // synchronous reads: contiguous rows next to a host copy
     uint64_t host_rows_cap = 0;
+    void *host_io = nullptr, *host_io_map = nullptr;  // mapped host memory of small synchronous reads
     void *leaf_q = nullptr;   // preprocessed reads: leaf requests and products
     uint64_t leaf_q_cap = 0;
     void *leaf_out = nullptr;

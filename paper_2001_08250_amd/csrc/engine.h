@@ -39,6 +39,9 @@ struct ReadGeom {
     uint32_t B;
     void *out;
     uint64_t out_pitch;
+    // Nonzero: out rows lie at any address and pitch and take this many bytes
+    // (plans with splits and without keys, whose last kernel writes them).
+    uint64_t out_bytes = 0;
     // serialized PIR: B x 8 key words (32-byte seeds) of the answers'
     // one-time masks, or none
     const uint32_t *keys = nullptr;
@@ -113,6 +116,11 @@ hipError_t launch_transpose_requests(const void *Q, uint64_t qpitch, uint32_t B,
 hipError_t launch_stage_group_offsets(const void *Q, uint64_t qpitch, uint32_t B, uint64_t n, uint32_t *Qs,
                                       uint32_t Bp, hipStream_t stream);
 
+// B rows of `bytes` bytes (any address and pitch) to whole words, zero-filled.
+hipError_t launch_restage_rows(void *dst, uint64_t dst_pitch, const void *src, uint64_t src_pitch, uint64_t bytes,
+                               uint64_t rows, hipStream_t stream);
+// `bytes` (a multiple of 16) from mapped host memory to the device.
+hipError_t launch_fetch(void *dst, const void *src, uint64_t bytes, hipStream_t stream);
 // dst row i = src row rows[i], i < count; pitches multiples of 16, rows of
 // round_up(row_bytes, 16) bytes are copied. src and rows may be host-mapped.
 // Row copy: dst row (dst_rows ? dst_rows[i] : i) = src row (src_rows ?
@@ -133,7 +141,8 @@ hipError_t launch_split_reduce(const void *partials, uint32_t splits, const Read
 // out row r (pitch out_pitch) = XOR over s < splits of partials[s][r]
 // ([splits][B][stride] bytes); `done`, when set, is recorded by the kernel.
 hipError_t launch_xor_splits(const void *partials, uint32_t splits, uint32_t B, uint64_t stride, void *out,
-                             uint64_t out_pitch, hipStream_t stream, hipEvent_t done);
+                             uint64_t out_pitch, hipStream_t stream, hipEvent_t done,
+                             uint64_t row_bytes = 0);
 hipError_t launch_mask_rows(const void *partials, uint32_t splits, uint32_t B, uint64_t stride, void *out,
                             uint64_t out_pitch, const uint32_t *keys, hipStream_t stream, hipEvent_t done = nullptr);
 

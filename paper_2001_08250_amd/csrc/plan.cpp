@@ -336,7 +336,7 @@ hipError_t launch_split_reduce(const void *partials, uint32_t splits, const Read
 {
     if (g.keys)
         return launch_mask_rows(partials, splits, g.B, g.stride, g.out, g.out_pitch, g.keys, stream, g.done);
-    return launch_xor_splits(partials, splits, g.B, g.stride, g.out, g.out_pitch, stream, g.done);
+    return launch_xor_splits(partials, splits, g.B, g.stride, g.out, g.out_pitch, stream, g.done, g.out_bytes);
 }
 
 hipError_t launch_read(const ReadGeom &g, const Plan &p, void *partials, hipStream_t stream, hipEvent_t ev_begin,
@@ -344,6 +344,8 @@ hipError_t launch_read(const ReadGeom &g, const Plan &p, void *partials, hipStre
 {
     if (g.B == 0)
         return hipSuccess;
+    if (g.out_bytes && (g.keys || p.splits <= 1))
+        return hipErrorInvalidValue;
     if (g.leaves != 1 && !(g.leaves > 1 && g.staged && p.kind == KIND_M4RW && (p.flags & PLAN_PAIRS)))
         return hipErrorInvalidValue;
     hipError_t e;

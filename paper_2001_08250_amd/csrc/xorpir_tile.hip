@@ -206,12 +206,16 @@ __global__ __launch_bounds__(WG) void xorpir_tile_kernel(const TileArgs a)
 // resp[r][c] = XOR over s of partials[s][r][c]. A workgroup covers TI
 // consecutive 16-byte words; its WG / TI thread groups take every
 // (WG / TI)-th split from their own first one and combine their sums in LDS.
+// row_bytes > 0: rows of that many bytes at any address (out, out_pitch);
+// writing them here saves such a read a copy of its answers (24 requests for
+// 999-byte buckets 22.4 us, 24.6 with it).
 // Few words and many splits (a batch of one request split over every bucket
 // range) thus still spread the partials over many threads.
 template <int TI>
 __global__ __launch_bounds__(WG) void xor_splits_kernel(const uint4 *__restrict__ P, uint64_t split16,
                                                         uint32_t splits, uint64_t count, uint32_t stride16,
-                                                        uint4 *__restrict__ out, uint64_t out_row16)
+                                                        uint4 *__restrict__ out, uint64_t out_pitch,
+                                                        uint64_t row_bytes)
 {
     constexpr uint32_t TS = WG / TI;
     const uint32_t t = threadIdx.x;
@@ -249,7 +253,18 @@ __global__ __launch_bounds__(WG) void xor_splits_kernel(const uint4 *__restrict_
     }
     if (sg == 0 && i < count) {
         const uint64_t r = i / stride16, c = i % stride16;
-        out[r * out_row16 + c] = acc;
+        uint8_t *o = reinterpret_cast<uint8_t *>(out) + r * out_pitch + c * 16;
+        if (row_bytes == 0) {
+            *reinterpret_cast<uint4 *>(o) = acc;
+        } else if (c * 16 + 16 <= row_bytes) {
+            __builtin_memcpy(o, &acc, 16);  // any alignment
+        } else {
+            const uint32_t w[4] = {acc.x, acc.y, acc.z, acc.w};
+#pragma unroll
+            for (uint32_t k = 0; k < 16; ++k)
+                if (c * 16 + k < row_bytes)
+                    o[k] = (uint8_t)(w[k / 4] >> (8 * (k % 4)));
+        }
     }
 }
 
@@ -310,14 +325,14 @@ static uint32_t split_reduce_items(uint64_t count, uint32_t splits)
 }
 
 hipError_t launch_xor_splits(const void *partials, uint32_t splits, uint32_t B, uint64_t stride, void *out,
-                             uint64_t out_pitch, hipStream_t stream, hipEvent_t done)
+                             uint64_t out_pitch, hipStream_t stream, hipEvent_t done, uint64_t row_bytes)
 {
     const uint32_t stride16 = (uint32_t)(stride / 16);
     const uint64_t count = (uint64_t)B * stride16;
     if (count == 0)
         return done ? hipEventRecord(done, stream) : hipSuccess;
     const uint32_t ti = split_reduce_items(count, splits);
-    void (*fn)(const uint4 *, uint64_t, uint32_t, uint64_t, uint32_t, uint4 *, uint64_t);
+    void (*fn)(const uint4 *, uint64_t, uint32_t, uint64_t, uint32_t, uint4 *, uint64_t, uint64_t);
     switch (ti) {
     case 4: fn = xor_splits_kernel<4>; break;
     case 8: fn = xor_splits_kernel<8>; break;
@@ -330,7 +345,7 @@ hipError_t launch_xor_splits(const void *partials, uint32_t splits, uint32_t B, 
     const uint32_t rgrid = (uint32_t)((count + ti - 1) / ti);
     hipExtLaunchKernelGGL(fn, dim3(rgrid), dim3(WG), 0, stream, nullptr, done, 0,
                           static_cast<const uint4 *>(partials), count, splits, count, stride16,
-                          static_cast<uint4 *>(out), out_pitch / 16);
+                          static_cast<uint4 *>(out), out_pitch, row_bytes);
     return hipGetLastError();
 }
 
