@@ -240,7 +240,9 @@ enum pir_kernel_kind {
  * PAIRS, 5-bucket tables or PAIR_G6's 6-bucket ones): 512-byte table
  * entries, each 32-lane half of a wave serving its own request, so a
  * workgroup answers twice the requests from one set of tables (tile =
- * requests per wave, 64 or 32). */
+ * requests per wave, 64 or 32). ONE_LAUNCH (MASK; tile 1, 2, 4 or 8, unroll
+ * 4): a workgroup takes 64 bytes of every bucket row, so one launch without
+ * splits answers the batch. */
 enum {
     PIR_PLAN_SHARED_COLUMN = 1,
     PIR_PLAN_ROLLING = 1 << 12,
@@ -248,7 +250,8 @@ enum {
     PIR_PLAN_PAIR_G4 = 1 << 14,
     PIR_PLAN_PAIR_G3 = 2 << 14,
     PIR_PLAN_HALF_WAVES = 1 << 16,
-    PIR_PLAN_PAIR_G6 = 1 << 17
+    PIR_PLAN_PAIR_G6 = 1 << 17,
+    PIR_PLAN_ONE_LAUNCH = 1 << 18
 };
 
 /* A read schedule: kernel family, request tile (requests per wave; MFMA:

@@ -40,7 +40,7 @@ struct ReadGeom {
     void *out;
     uint64_t out_pitch;
     // Nonzero: out rows lie at any address and pitch and take this many bytes
-    // (plans with splits and without keys, whose last kernel writes them).
+    // (reads without keys under plans that writes_any_row accepts).
     uint64_t out_bytes = 0;
     // serialized PIR: B x 8 key words (32-byte seeds) of the answers'
     // one-time masks, or none
@@ -68,6 +68,7 @@ struct Plan {
     uint32_t flags;    // PLAN_SHARED_COLUMN
 };
 constexpr uint32_t PLAN_SHARED_COLUMN = 1;
+constexpr uint32_t PLAN_ONE_LAUNCH = 1u << 18;  // whole bucket range per workgroup, no splits
 constexpr uint32_t PLAN_ROLLING = 1u << 12;
 // paired tables of 5 - ((flags >> PLAN_PAIR_G_SHIFT) & 3) buckets each (5, 4 or 3)
 constexpr uint32_t PLAN_PAIR_G_SHIFT = 14;
@@ -82,6 +83,8 @@ uint64_t partial_bytes(const ReadGeom &g, const Plan &p);
 
 // Fill in a complete plan (tile, splits, unroll) for geometry g from a
 // partial request (kind may be AUTO; zero fields mean "choose").
+// Whether a read under p without keys writes answer rows at any alignment.
+inline bool writes_any_row(const Plan &p) { return p.splits > 1 || (p.flags & PLAN_ONE_LAUNCH); }
 Plan resolve_plan(const ReadGeom &g, Plan want, int num_cus);
 // Bucket splits for one launch of `leaves` products of geometry g under plan p.
 uint32_t leaf_splits(const ReadGeom &g, const Plan &p, uint32_t leaves, int num_cus);

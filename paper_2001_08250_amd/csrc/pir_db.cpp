@@ -912,7 +912,7 @@ static int read_sync(pir_db *db, const uint8_t *req_bits, uint32_t B, const uint
     } else {
         Plan p = choose_plan(db, B, qp);
         PIR_TRY(ensure_device(&sc.part, &sc.part_cap, partial_bytes(g, p)));
-        if (out_bytes <= HOST_IO && p.splits > 1 && !g.keys) {
+        if (out_bytes <= HOST_IO && writes_any_row(p) && !g.keys) {
             r_mapped = true;
             g.out = static_cast<uint8_t *>(sc.host_io_map) + HOST_IO;
             g.out_pitch = g.out_bytes = db->bucket_bytes;
@@ -980,8 +980,8 @@ static int read_async(pir_db *db, const void *d_req, uint64_t req_pitch, uint32_
     } else {
         Plan p = choose_plan(db, B, qp);
         PIR_TRY(ensure_device(&sc.part, &sc.part_cap, partial_bytes(g, p)));
-        // the split reduction writes answer rows at any alignment
-        const bool bytes = !direct && p.splits > 1 && !d_keys;
+        // a split reduction writes answer rows at any alignment
+        const bool bytes = !direct && writes_any_row(p) && !d_keys;
         if (bytes) {
             g.out = d_resp;
             g.out_pitch = resp_pitch;

@@ -205,8 +205,12 @@ Plan resolve_plan(const ReadGeom &g, Plan want, int num_cus)
             p.unroll = 8;
             p.tile = g.B > 64 ? 16 : g.B > 32 ? 8 : 4;
         } else {
-            // Masked XOR. A database that the caches hold (up to 64 MiB) is
-            // read by as many waves as there are; from 5 to 8 requests two
+            // Masked XOR. One launch while its few workgroups, one per 64
+            // bytes of a row, take less time than a second launch: 8 requests
+            // over 1024 buckets 7.2 against 10.2 us, one over 4096 7.2 against
+            // 9.5, 4 over 4096 10.8 against 10.6, 8 17 against 11, one over
+            // 8192 of 4 KiB 11.6 against 10.0. Else a database that the caches
+            // hold (up to 64 MiB) is read by as many waves as there are; from 5 to 8 requests two
             // waves of 4 share a 1 KiB column chunk, which halves the chain
             // of scalar work per bucket (8 requests over 4 MiB 11.3 us, one
             // wave's tile of 8 13.3, over 64 MiB 19.7 and 20.5). A larger one
@@ -218,7 +222,12 @@ Plan resolve_plan(const ReadGeom &g, Plan want, int num_cus)
             // 512 bytes and less as half a chunk (4 requests over 256 MiB of
             // 512-byte rows 51 against 53 us, of 256-byte rows 58 against 86).
             p.kind = KIND_MASK;
-            if (bytes > (64ull << 20)) {
+            const uint32_t one = pow2_at_least(std::max<uint32_t>(g.B, 1));
+            if (g.B <= 8 && g.n <= 4096 && g.n * one <= 8192 && bytes <= (16ull << 20)) {
+                p.flags = PLAN_ONE_LAUNCH;
+                p.tile = one;
+                p.unroll = 4;
+            } else if (bytes > (64ull << 20)) {
                 p.tile = pow2_at_least(std::max<uint32_t>(g.B, 1));
                 p.unroll = 8;
                 const uint64_t waves = 4ull * std::max(num_cus, 1);
@@ -265,6 +274,13 @@ Plan resolve_plan(const ReadGeom &g, Plan want, int num_cus)
         // 3-bucket tables (64 / 32 KiB) let two workgroups share it
         per_cu = ((p.flags & PLAN_PAIRS) && ((p.flags >> PLAN_PAIR_G_SHIFT) & 3u)) ? 2 : 1;
     } else {
+        if (p.flags & PLAN_ONE_LAUNCH) {
+            p.splits = 1;
+            if (p.unroll == 0)
+                p.unroll = 4;
+            if (p.tile == 0)
+                p.tile = 8;
+        }
         if (p.tile == 0)
             p.tile = g.B <= 16 ? pow2_at_least(std::max<uint32_t>(g.B, 1)) : 16;
         if (p.unroll == 0)
@@ -344,7 +360,7 @@ hipError_t launch_read(const ReadGeom &g, const Plan &p, void *partials, hipStre
 {
     if (g.B == 0)
         return hipSuccess;
-    if (g.out_bytes && (g.keys || p.splits <= 1))
+    if (g.out_bytes && (g.keys || !writes_any_row(p)))
         return hipErrorInvalidValue;
     if (g.leaves != 1 && !(g.leaves > 1 && g.staged && p.kind == KIND_M4RW && (p.flags & PLAN_PAIRS)))
         return hipErrorInvalidValue;
@@ -361,7 +377,7 @@ hipError_t launch_read(const ReadGeom &g, const Plan &p, void *partials, hipStre
     if (e == hipSuccess && p.splits <= 1) {
         if (g.keys)
             e = launch_mask_rows(nullptr, 0, g.leaves * g.B, g.stride, g.out, g.out_pitch, g.keys, stream, g.done);
-        else if (g.done)
+        else if (g.done && (ev_end || !(p.flags & PLAN_ONE_LAUNCH)))
             e = hipEventRecord(g.done, stream);
     }
     return e;

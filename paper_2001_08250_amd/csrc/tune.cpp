@@ -116,6 +116,8 @@ int pir_tune(pir_db *db, uint32_t B, uint32_t iters, pir_plan *best, double *bes
             }
         }
     }
+    if (B <= 8 && db->n <= 16384)
+        cands.push_back(resolve_plan(g, Plan{KIND_MASK, 8, 1, 4, PLAN_ONE_LAUNCH}, db->num_cus));
     for (uint32_t t : {32u, 64u, 96u, 128u}) {
         if (t > 2 * std::max<uint32_t>(B, 16))
             continue;
