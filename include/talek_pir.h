@@ -241,8 +241,8 @@ enum pir_kernel_kind {
  * entries, each 32-lane half of a wave serving its own request, so a
  * workgroup answers twice the requests from one set of tables (tile =
  * requests per wave, 64 or 32). ONE_LAUNCH (MASK; tile 1, 2, 4 or 8, unroll
- * 4): a workgroup takes 64 bytes of every bucket row, so one launch without
- * splits answers the batch. */
+ * 4, no other flag; ignored with others): a workgroup takes 64 bytes of every
+ * bucket row, so one launch without splits answers the batch. */
 enum {
     PIR_PLAN_SHARED_COLUMN = 1,
     PIR_PLAN_ROLLING = 1 << 12,

@@ -83,8 +83,14 @@ uint64_t partial_bytes(const ReadGeom &g, const Plan &p);
 
 // Fill in a complete plan (tile, splits, unroll) for geometry g from a
 // partial request (kind may be AUTO; zero fields mean "choose").
+// Whether p is the one-launch kernel's plan.
+inline bool one_launch(const Plan &p)
+{
+    return p.kind == KIND_MASK && p.flags == PLAN_ONE_LAUNCH && p.unroll == 4 &&
+           (p.tile == 1 || p.tile == 2 || p.tile == 4 || p.tile == 8);
+}
 // Whether a read under p without keys writes answer rows at any alignment.
-inline bool writes_any_row(const Plan &p) { return p.splits > 1 || (p.flags & PLAN_ONE_LAUNCH); }
+inline bool writes_any_row(const Plan &p) { return p.splits > 1 || one_launch(p); }
 Plan resolve_plan(const ReadGeom &g, Plan want, int num_cus);
 // Bucket splits for one launch of `leaves` products of geometry g under plan p.
 uint32_t leaf_splits(const ReadGeom &g, const Plan &p, uint32_t leaves, int num_cus);

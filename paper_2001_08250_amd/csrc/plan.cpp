@@ -275,11 +275,11 @@ Plan resolve_plan(const ReadGeom &g, Plan want, int num_cus)
         per_cu = ((p.flags & PLAN_PAIRS) && ((p.flags >> PLAN_PAIR_G_SHIFT) & 3u)) ? 2 : 1;
     } else {
         if (p.flags & PLAN_ONE_LAUNCH) {
-            p.splits = 1;
-            if (p.unroll == 0)
-                p.unroll = 4;
-            if (p.tile == 0)
-                p.tile = 8;
+            const Plan one{p.kind, p.tile ? p.tile : 8, 1, p.unroll ? p.unroll : 4, p.flags};
+            if (one_launch(one))
+                p = one;
+            else
+                p.flags &= ~PLAN_ONE_LAUNCH;  // a tile plan as without the flag
         }
         if (p.tile == 0)
             p.tile = g.B <= 16 ? pow2_at_least(std::max<uint32_t>(g.B, 1)) : 16;
@@ -377,7 +377,7 @@ hipError_t launch_read(const ReadGeom &g, const Plan &p, void *partials, hipStre
     if (e == hipSuccess && p.splits <= 1) {
         if (g.keys)
             e = launch_mask_rows(nullptr, 0, g.leaves * g.B, g.stride, g.out, g.out_pitch, g.keys, stream, g.done);
-        else if (g.done && (ev_end || !(p.flags & PLAN_ONE_LAUNCH)))
+        else if (g.done && (ev_end || !one_launch(p)))
             e = hipEventRecord(g.done, stream);
     }
     return e;

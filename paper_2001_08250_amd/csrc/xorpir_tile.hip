@@ -390,17 +390,11 @@ TileFn pick_tile_u(uint32_t T, uint32_t U, bool share)
 
 TileFn tile_fn(const Plan &p, bool once)
 {
-    if (p.flags & PLAN_ONE_LAUNCH) {
-        if (p.kind != KIND_MASK || p.unroll != 4 || p.flags != PLAN_ONE_LAUNCH)
-            return nullptr;
-        switch (p.tile) {
-        case 1: return xorpir_small_kernel<1>;
-        case 2: return xorpir_small_kernel<2>;
-        case 4: return xorpir_small_kernel<4>;
-        case 8: return xorpir_small_kernel<8>;
-        default: return nullptr;
-        }
-    }
+    if (one_launch(p))
+        return p.tile == 1   ? xorpir_small_kernel<1>
+               : p.tile == 2 ? xorpir_small_kernel<2>
+               : p.tile == 4 ? xorpir_small_kernel<4>
+                             : xorpir_small_kernel<8>;
     const bool share = p.flags & PLAN_SHARED_COLUMN;
     if (p.kind == KIND_MASK)
         return once ? pick_tile_u<KIND_MASK, true>(p.tile, p.unroll, share)
@@ -469,7 +463,7 @@ hipError_t launch_tile_read(const ReadGeom &g, const Plan &p, void *partials, hi
     a.B = g.B;
     a.Q = static_cast<const uint32_t *>(g.Q);
     a.qpitch_w = g.qpitch / 4;
-    if (p.flags & PLAN_ONE_LAUNCH) {
+    if (one_launch(p)) {
         if (p.splits != 1)
             return hipErrorInvalidValue;
         a.n_rt = (g.B + p.tile - 1) / p.tile;

@@ -60,7 +60,7 @@ def test_counts_up_to_the_split_limit(n):
                 assert (db.read(q) == want).all(), (tile, splits)
 
 
-@pytest.mark.parametrize("n,d,z", [(1000, 3, 100), (2000, 4, 260), (5000, 1, 48), (8200, 1, 2000), (70000, 1, 64)])
+@pytest.mark.parametrize("n,d,z", [(1000, 3, 100), (2000, 4, 260), (4128, 1, 512), (8160, 2, 64), (5000, 1, 48), (8200, 1, 2000), (70000, 1, 64)])
 def test_automatic_choice_equals_the_masked_kernel(n, d, z):
     """Pitched and unaligned requests and answers, masked answers, from the
     smallest batch that takes the matrix cores to beyond the tables'."""
@@ -81,12 +81,15 @@ def test_automatic_choice_equals_the_masked_kernel(n, d, z):
             kinds.add(db.get_plan(B).kind)
             say(f"n={n} d={d} z={z} B={B} kind={db.get_plan(B).kind}")
             db.read_async(q, out)
-            plain = torch.zeros_like(ref)
-            db.read_async(req, plain)
+            plain, near = torch.zeros_like(ref), torch.zeros_like(ref)
+            db.read_async(req, plain)        # in place where rows are whole words (4128 and 8160 buckets)
+            at4 = torch.zeros((B, nb + 8), dtype=torch.uint8, device=dev)[:, 4:4 + nb]
+            at4.copy_(req)
+            db.read_async(at4, near)
             db.set_plan(pir.KERNEL_MASK)
             db.read_async(req, ref)
             torch.cuda.synchronize()
-            assert torch.equal(out, ref) and torch.equal(plain, ref), B
+            assert torch.equal(out, ref) and torch.equal(plain, ref) and torch.equal(near, ref), B
             assert not big[:, :5].any() and not big[:, 5 + d * z:].any()
         assert pir.KERNEL_MFMA in kinds
 

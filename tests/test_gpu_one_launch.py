@@ -56,8 +56,9 @@ def test_range_of_the_automatic_choice():
             for B in (1, 2, 4, 8, 9):
                 p = db.get_plan(B)
                 assert (p.flags == pir.PLAN_ONE_LAUNCH and p.splits == 1) == (B in one or (n == 16 and B < 9)), (n, row, B)
-            for tile, unroll, flags in ((16, 4, 0), (8, 8, 0), (8, 4, pir.PLAN_SHARED_COLUMN)):
-                with pytest.raises(pir.PirError):
-                    db.set_plan(pir.KERNEL_MASK, tile, 0, unroll, flags | pir.PLAN_ONE_LAUNCH)
-            with pytest.raises(pir.PirError):
-                db.set_plan(pir.KERNEL_SKIP, 8, 0, 4, pir.PLAN_ONE_LAUNCH)
+            for kind, tile, unroll, flags in ((pir.KERNEL_MASK, 16, 4, 0), (pir.KERNEL_MASK, 8, 8, 0), (pir.KERNEL_SKIP, 8, 4, 0),
+                                              (pir.KERNEL_MASK, 8, 4, pir.PLAN_SHARED_COLUMN)):
+                db.set_plan(kind, tile, 3, unroll, flags | pir.PLAN_ONE_LAUNCH)   # the plan without the flag
+                p = db.get_plan(4)
+                assert (p.kind, p.tile, p.unroll, p.flags) == (kind, tile, unroll, flags)
+            db.set_plan()
