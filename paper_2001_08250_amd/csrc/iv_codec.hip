@@ -96,11 +96,14 @@ __device__ __forceinline__ uint64_t before(uint64_t v, uint64_t *all)
 }
 
 // Whether this is the pass's last workgroup; it sees what the others' first
-// threads stored, and every atomic. (One release a workgroup: a fence by every
-// thread, each a write-back of the L2, took 20 us a pass.)
+// threads stored, and every atomic: each wave waits for its own before the
+// barrier, which by itself waits for no other wave's memory operations. (One
+// release a workgroup: a fence by every thread, each a write-back of the L2,
+// took 20 us a pass.)
 __device__ __forceinline__ bool last_workgroup(CodecState *st, uint32_t tiles)
 {
     __shared__ bool last;
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
     __syncthreads();
     if (threadIdx.x == 0) {
         last = __hip_atomic_fetch_add(&st->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == tiles - 1;
