@@ -243,6 +243,7 @@ static int cuckoo_new(pir_db *db, uint64_t n, uint32_t d, uint32_t z, uint64_t c
         c->table.assign(n * d * (uint64_t)z, 0);
         c->occupant.assign(n * d, -1);
         c->changed.assign(n, 0);
+        c->changed_list.reserve(n);  // a walk allocates nothing: half done, its bytes are not where its messages are
         c->carry.resize(z);
         c->spare.resize(z);
         c->turn.resize(z);
