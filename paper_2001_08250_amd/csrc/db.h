@@ -29,7 +29,6 @@ struct Scratch {
     uint64_t keys_cap = 0;
     void *host_rows = nullptr;  // synchronous reads: contiguous rows next to a host copy
     uint64_t host_rows_cap = 0;
-    void *host_io = nullptr, *host_io_map = nullptr;  // mapped host memory of small synchronous reads
     void *leaf_q = nullptr;   // preprocessed reads: leaf requests and products
     uint64_t leaf_q_cap = 0;
     void *leaf_out = nullptr;
@@ -79,6 +78,9 @@ struct pir_db {
     uint64_t *stage_idx_host = nullptr;
     void *stage_map = nullptr;
     void *stage_idx_map = nullptr;
+    // behind the indices: mapped memory for the rows of small synchronous
+    // reads (its requests, then its answers), or null
+    uint8_t *io_host = nullptr, *io_map = nullptr;
     uint64_t stage_cap = 0;   // rows
     uint64_t stage_rows = 0;
     std::unordered_map<uint64_t, uint64_t> stage_slot;

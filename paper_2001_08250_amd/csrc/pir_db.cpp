@@ -127,6 +127,11 @@ namespace {
 
 constexpr uint64_t STAGE_BYTES = 64ull << 20;  // pinned staging for bucket writes
 
+// Request bytes, and answer bytes, of a synchronous read that go through
+// mapped host memory: 64 answers of 4 KiB take 40 us with it and 51 without,
+// 128 52 and 64, 256 104 and 100.
+constexpr uint64_t HOST_IO = 512 << 10;
+
 #define HIP_TRY(x)                                                                                                 \
     do {                                                                                                           \
         hipError_t e_ = (x);                                                                                       \
@@ -274,8 +279,6 @@ void free_db(pir_db *db)
         hipFree(kv.second.aux);
         hipFree(kv.second.keys);
         hipFree(kv.second.leaf_q);
-        if (kv.second.host_io)
-            hipHostFree(kv.second.host_io);
         hipFree(kv.second.host_rows);
         hipFree(kv.second.leaf_out);
     }
@@ -400,8 +403,17 @@ int pir_db_create(uint64_t n, uint32_t d, uint32_t msg_bytes, pir_db **out)
         if ((rc = host_mapped(db->stage_cap * stride, &p, &db->stage_map)) != PIR_OK)
             break;
         db->stage_host = static_cast<uint8_t *>(p);
-        if ((rc = host_mapped(db->stage_cap * sizeof(uint64_t), &p, &db->stage_idx_map)) != PIR_OK)
+        // their indices, and room for the rows of small synchronous reads, here
+        // so that no such read pays for it (a handle's first one over 10 MiB 30
+        // us, 45-57 with the allocation in it); without it their rows are copied
+        const uint64_t idx_bytes = (db->stage_cap * sizeof(uint64_t) + 255) & ~255ull;
+        rc = host_mapped(idx_bytes + 2 * HOST_IO, &p, &db->stage_idx_map);
+        if (rc == PIR_OK) {
+            db->io_host = static_cast<uint8_t *>(p) + idx_bytes;
+            db->io_map = static_cast<uint8_t *>(db->stage_idx_map) + idx_bytes;
+        } else if ((rc = host_mapped(idx_bytes, &p, &db->stage_idx_map)) != PIR_OK) {
             break;
+        }
         db->stage_idx_host = static_cast<uint64_t *>(p);
         db->dirty_mark.assign(n, 0);
         // the paper's sizes: a vector of about 14 KB at 1M messages and a TTL
@@ -849,11 +861,6 @@ static int prep_read(pir_db *db, Scratch &sc, const LeafRead &lr, uint32_t B, vo
     return PIR_OK;
 }
 
-// Request bytes, and answer bytes, of a synchronous read that go through
-// mapped host memory: 64 answers of 4 KiB take 40 us with it and 51 without,
-// 128 52 and 64, 256 104 and 100.
-constexpr uint64_t HOST_IO = 512 << 10;
-
 static bool use_prep(const pir_db *db, uint32_t B) { return db->prep && B >= db->prep_min_batch; }
 
 // Synchronous read (host rows in and out); seeds = B x 32 bytes of mask
@@ -870,25 +877,23 @@ static int read_sync(pir_db *db, const uint8_t *req_bits, uint32_t B, const uint
     // bytes go through mapped host memory instead, a kernel fetching the
     // requests and the read's last one writing the answers: the runtime's
     // copies, each with a staging buffer and a wait of its own, made up half
-    // of such a call's time (one request over 10 MiB @@ us, 38 with them).
+    // of such a call's time (one request over 10 MiB 24 us, 38 with them).
     const uint64_t qb = db->qbytes, in_bytes = (uint64_t)B * qb, out_bytes = (uint64_t)B * db->bucket_bytes;
     const uint64_t in_dev = ((uint64_t)B * db->qpitch + 15) & ~15ull;
-    const bool q_mapped = in_dev <= HOST_IO;
+    const bool q_mapped = db->io_host && in_dev <= HOST_IO;
     const bool q_direct = q_mapped || qb % 4 == 0, r_direct = db->stride == db->bucket_bytes;
-    if (!sc.host_io && (q_mapped || out_bytes <= HOST_IO))
-        PIR_TRY(host_mapped(2 * HOST_IO, &sc.host_io, &sc.host_io_map));
     if (!q_direct || !r_direct)
         PIR_TRY(ensure_device(&sc.host_rows, &sc.host_rows_cap, std::max(q_direct ? 0 : in_bytes,
                                                                            r_direct ? 0 : out_bytes)));
     uint64_t qp = q_mapped ? db->qpitch : qb;
     if (q_mapped) {
-        uint8_t *rows = static_cast<uint8_t *>(sc.host_io);
+        uint8_t *rows = db->io_host;
         for (uint32_t r = 0; r < B; ++r) {
             memcpy(rows + r * qp, req_bits + r * qb, qb);
             memset(rows + r * qp + qb, 0, qp - qb);
         }
         PIR_TRY(ensure_device(&sc.req, &sc.req_cap, in_dev));
-        HIP_TRY(launch_fetch(sc.req, sc.host_io_map, in_dev, db->stream));
+        HIP_TRY(launch_fetch(sc.req, db->io_map, in_dev, db->stream));
     } else if (q_direct) {
         HIP_TRY(hipMemcpyAsync(sc.req, req_bits, in_bytes, hipMemcpyHostToDevice, db->stream));
     } else {
@@ -912,16 +917,16 @@ static int read_sync(pir_db *db, const uint8_t *req_bits, uint32_t B, const uint
     } else {
         Plan p = choose_plan(db, B, qp);
         PIR_TRY(ensure_device(&sc.part, &sc.part_cap, partial_bytes(g, p)));
-        if (out_bytes <= HOST_IO && writes_any_row(p) && !g.keys) {
+        if (db->io_host && out_bytes <= HOST_IO && writes_any_row(p) && !g.keys) {
             r_mapped = true;
-            g.out = static_cast<uint8_t *>(sc.host_io_map) + HOST_IO;
+            g.out = db->io_map + HOST_IO;
             g.out_pitch = g.out_bytes = db->bucket_bytes;
         }
         HIP_TRY(launch_read(g, p, sc.part, db->stream, eb, ee));
     }
     if (r_mapped) {
         HIP_TRY(hipStreamSynchronize(db->stream));
-        memcpy(resp, static_cast<uint8_t *>(sc.host_io) + HOST_IO, out_bytes);
+        memcpy(resp, db->io_host + HOST_IO, out_bytes);
         return PIR_OK;
     }
     if (r_direct) {
