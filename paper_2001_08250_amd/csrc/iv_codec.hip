@@ -11,7 +11,8 @@
 // bits and its last one, from which the launch's last workgroup has c, k and
 // the position set just before each tile; every tile's code bits, from which
 // it has their offsets; and the codes, ORed into the zeroed body, whose start
-// it writes to mapped host memory. The host waits once.
+// it writes to mapped host memory. The host waits once, and a second time for
+// what a body has past its first 64 KiB.
 //
 // What bounds it: launches and waits, not the vector (0.6 MB at the 100K
 // messages' size). Library scans over single words and single codes took 11
@@ -38,7 +39,8 @@ struct CodecState {
     uint32_t done;  // workgroups of the running pass that have finished
 };
 
-// The result, in mapped host memory: the body's first DIRECT bytes follow.
+// The result, in mapped host memory (or, without it, on the device): the body's
+// first DIRECT bytes follow.
 struct CodecResult {
     uint64_t c, bits, k, pad;
 };
@@ -285,15 +287,18 @@ int encode_interest(pir_db *db, const uint32_t *words, uint64_t m, uint8_t *out,
     // c < m / 2^k for k > 0, and m for k = 0.
     const uint64_t body_words = (m + m / 2 + 31) / 32 + 1;
     if (!db->codec) {
-        int rc = ensure_device(&db->codec, &db->codec_cap, sizeof(CodecState));
+        (void)host_mapped(sizeof(CodecResult) + DIRECT, &db->codec_host, &db->codec_map);
+        const uint64_t result = db->codec_host ? 0 : sizeof(CodecResult) + DIRECT;
+        int rc = ensure_device(&db->codec, &db->codec_cap, sizeof(CodecState) + result);
         if (rc == PIR_OK && launch_fill_zero(db->codec, sizeof(CodecState), s) != hipSuccess)
             rc = PIR_EDEVICE;
-        if (rc == PIR_OK && !db->codec_host)
-            rc = host_mapped(sizeof(CodecResult) + DIRECT, &db->codec_host, &db->codec_map);
         if (rc != PIR_OK) {
             hipFree(db->codec);
             db->codec = nullptr;
             db->codec_cap = 0;
+            if (db->codec_host)
+                hipHostFree(db->codec_host);
+            db->codec_host = nullptr;
             return rc;
         }
     }
@@ -303,7 +308,7 @@ int encode_interest(pir_db *db, const uint32_t *words, uint64_t m, uint8_t *out,
     a.st = static_cast<CodecState *>(db->codec);
     a.count = static_cast<uint64_t *>(db->codec2);
     a.length = a.count + a.tiles;
-    a.result = static_cast<CodecResult *>(db->codec_map);
+    a.result = db->codec_host ? static_cast<CodecResult *>(db->codec_map) : reinterpret_cast<CodecResult *>(a.st + 1);
     if (out) {
         rc = ensure_device(&db->codec3, &db->codec3_cap, body_words * 4);
         if (rc != PIR_OK)
@@ -317,7 +322,12 @@ int encode_interest(pir_db *db, const uint32_t *words, uint64_t m, uint8_t *out,
         hipLaunchKernelGGL(codec_write_kernel, dim3(a.tiles), dim3(WG), 0, s, a);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
         return PIR_EDEVICE;
-    const CodecResult res = *static_cast<const CodecResult *>(db->codec_host);
+    CodecResult res;
+    if (db->codec_host)
+        res = *static_cast<const CodecResult *>(db->codec_host);
+    else if (hipMemcpyAsync(&res, a.result, sizeof res, hipMemcpyDeviceToHost, s) != hipSuccess ||
+             hipStreamSynchronize(s) != hipSuccess)
+        return PIR_EDEVICE;
     if (res.c > 0x7fffffffull)  // the stream's documented limit
         return PIR_EINVAL;
     const uint64_t bytes = (res.bits + 7) / 8, total = 24 + bytes;
@@ -335,8 +345,9 @@ int encode_interest(pir_db *db, const uint32_t *words, uint64_t m, uint8_t *out,
         out[16 + i] = (uint8_t)(res.k >> (8 * i));
         out[20 + i] = 0;
     }
-    const uint64_t direct = std::min(bytes, DIRECT);
-    std::memcpy(out + 24, static_cast<const CodecResult *>(db->codec_host) + 1, direct);
+    const uint64_t direct = db->codec_host ? std::min(bytes, DIRECT) : 0;
+    if (direct)
+        std::memcpy(out + 24, static_cast<const CodecResult *>(db->codec_host) + 1, direct);
     if (bytes > direct &&
         (hipMemcpyAsync(out + 24 + direct, reinterpret_cast<const uint8_t *>(a.body) + direct, bytes - direct,
                         hipMemcpyDeviceToHost, s) != hipSuccess ||

@@ -45,6 +45,7 @@ int host_mapped(uint64_t bytes, void **host, void **dev)
         return PIR_ENOMEM;
     }
     if (hipHostGetDevicePointer(dev, *host, 0) != hipSuccess) {
+        (void)hipGetLastError();
         hipHostFree(*host);
         *host = nullptr;
         return PIR_EDEVICE;

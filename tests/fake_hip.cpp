@@ -170,6 +170,12 @@ struct Db {
         std::vector<uint8_t> q(B * ((n + 7) / 8)), r(B * row);
         return pir_read_batch(h, q.data(), B, r.data());
     }
+    int encode()
+    {
+        std::vector<uint8_t> out(1 << 16);
+        uint64_t size = 0;
+        return pir_interest_vector_encoded(h, out.data(), out.size(), &size);
+    }
 };
 
 // A handle's first small read allocates no pinned memory and copies nothing.
@@ -194,6 +200,17 @@ void read_without_pinned_memory()
     CHECK(launched("fetch_kernel") == 0 && copies >= 4);
 }
 
+// Without pinned memory for the result, a code still is answered.
+void code_without_pinned_memory()
+{
+    Db db(256, 1, 64);
+    pinned_fail_from = 0;
+    const uint64_t copied = copies;
+    CHECK(db.encode() == PIR_OK && copies == copied + 1);
+    pinned_fail_from = UINT64_MAX;
+    CHECK(db.encode() == PIR_OK && copies == copied + 2);
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -201,6 +218,7 @@ int main(int argc, char **argv)
     const std::map<std::string, void (*)()> all = {
         {"first_read", first_read},
         {"read_without_pinned_memory", read_without_pinned_memory},
+        {"code_without_pinned_memory", code_without_pinned_memory},
     };
     const auto it = argc > 1 ? all.find(argv[1]) : all.end();
     if (it == all.end())
