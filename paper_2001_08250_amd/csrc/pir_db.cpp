@@ -795,8 +795,10 @@ static int prep_requests(pir_db *db, Scratch &sc, const void *q, uint64_t qp, ui
     g.leaf = true;
     Plan want = db->forced;
     if (want.kind == KIND_AUTO) {
+        // a matrix-core plan was tuned for a single product of this shape; the
+        // leaves' pair tables are staged together and take one launch
         Plan tuned;
-        if (tune_lookup(l.Nq, l.Bq, l.Cq, &tuned))
+        if (tune_lookup(l.Nq, l.Bq, l.Cq, &tuned) && tuned.kind != KIND_MFMA)
             want = tuned;
     }
     lr->p = resolve_plan(g, want, db->num_cus);

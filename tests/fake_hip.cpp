@@ -211,6 +211,29 @@ void code_without_pinned_memory()
     CHECK(db.encode() == PIR_OK && copies == copied + 2);
 }
 
+// A matrix-core plan tuned for a plain database of the leaves' shape leaves
+// their read as it is: staged together, one launch for all of them.
+void tuned_leaves()
+{
+    char path[] = "/tmp/fake_hip_plans_XXXXXX";
+    const int fd = mkstemp(path);
+    FILE *f = fdopen(fd, "w");
+    fprintf(f, "[\n {\"n\": 2048, \"bclass\": 256, \"stride\": 256, \"kind\": 5, \"tile\": 64, \"splits\": 2, "
+               "\"unroll\": 4, \"flags\": 0, \"us\": 20.0}\n]\n");
+    fclose(f);
+    CHECK(pir_tune_load(path) == PIR_OK);
+    remove(path);
+    Db db(8192, 1, 1024);  // 49 leaves of 2048 rows of 256 bytes, 256 requests each
+    CHECK(pir_preprocess(db.h, 2, 1) == PIR_OK);
+    launches.clear();
+    CHECK(db.read(1024) == PIR_OK);
+    CHECK(launched("xorpir_mfma_kernel") == 0 && launched("xorpir_m4r") == 1);
+    Db plain(2048, 1, 256);  // where the plan was tuned it is taken
+    launches.clear();
+    CHECK(plain.read(256) == PIR_OK);
+    CHECK(launched("xorpir_mfma_kernel") == 1);
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -219,6 +242,7 @@ int main(int argc, char **argv)
         {"first_read", first_read},
         {"read_without_pinned_memory", read_without_pinned_memory},
         {"code_without_pinned_memory", code_without_pinned_memory},
+        {"tuned_leaves", tuned_leaves},
     };
     const auto it = argc > 1 ? all.find(argv[1]) : all.end();
     if (it == all.end())
