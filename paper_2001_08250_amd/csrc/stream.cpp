@@ -150,7 +150,7 @@ extern "C" int pir_read_stream_async(pir_db *db, const void *d_req, uint64_t req
 
     // Signature of everything the captured graph bakes in.
     std::vector<uint64_t> sig;
-    sig.reserve(8 + 4 * groups.size() + idx.size());
+    sig.reserve(8 + 6 * groups.size() + idx.size());
     sig.push_back(reinterpret_cast<uintptr_t>(db->buf[db->front]));
     sig.push_back(reinterpret_cast<uintptr_t>(d_req));
     sig.push_back(req_pitch);
@@ -164,8 +164,9 @@ extern "C" int pir_read_stream_async(pir_db *db, const void *d_req, uint64_t req
         sig.push_back(((uint64_t)gr.B << 32) | (gr.gather ? 2u : 0u) | (gr.scatter ? 1u : 0u));
         sig.push_back(gr.req_row);
         sig.push_back(gr.resp_row);
-        sig.push_back(((uint64_t)p.kind << 56) ^ ((uint64_t)p.tile << 40) ^ ((uint64_t)p.unroll << 32) ^
-                      ((uint64_t)p.flags << 16) ^ p.splits);
+        sig.push_back(((uint64_t)p.kind << 32) | p.tile);
+        sig.push_back(((uint64_t)p.unroll << 32) | p.splits);
+        sig.push_back(p.flags);
     }
     sig.insert(sig.end(), idx.begin(), idx.end());
 

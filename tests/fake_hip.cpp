@@ -234,6 +234,31 @@ void tuned_leaves()
     CHECK(launched("xorpir_mfma_kernel") == 1);
 }
 
+// A stream captured under one plan is not replayed under another, whichever
+// fields differ.
+void stream_plans()
+{
+    const uint64_t n = 32 * 65600;
+    const uint32_t sizes[] = {5, 3}, B = 8;
+    Db db(n, 1, 16);
+    std::vector<uint8_t> q(B * n / 8), out(B * 16 + 16);
+    void *resp = reinterpret_cast<void *>((reinterpret_cast<uintptr_t>(out.data()) + 15) & ~15ull);
+    const pir_plan plans[] = {
+        {PIR_KERNEL_MASK, 8, 65537, 4, 0},
+        {PIR_KERNEL_MASK, 8, 1, 4, PIR_PLAN_SHARED_COLUMN},
+        {PIR_KERNEL_MASK, 8, 1, 4, 0},
+        {PIR_KERNEL_MASK, 8, 1, 4, PIR_PLAN_ONE_LAUNCH},
+        {PIR_KERNEL_MFMA, 32, 3, 4, 0},
+    };
+    for (const pir_plan &p : plans)
+        for (int again = 0; again < 2; ++again) {
+            CHECK(pir_set_plan(db.h, &p) == PIR_OK);
+            const uint64_t c = captures, r = replays;
+            CHECK(pir_read_stream_async(db.h, q.data(), n / 8, sizes, nullptr, 2, resp, 16, nullptr, nullptr) == PIR_OK);
+            CHECK(captures == c + !again && replays == r + 1);
+        }
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -243,6 +268,7 @@ int main(int argc, char **argv)
         {"read_without_pinned_memory", read_without_pinned_memory},
         {"code_without_pinned_memory", code_without_pinned_memory},
         {"tuned_leaves", tuned_leaves},
+        {"stream_plans", stream_plans},
     };
     const auto it = argc > 1 ? all.find(argv[1]) : all.end();
     if (it == all.end())
