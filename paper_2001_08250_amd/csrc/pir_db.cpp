@@ -874,7 +874,6 @@ static int read_sync(pir_db *db, const uint8_t *req_bits, uint32_t B, const uint
     HIP_TRY(hipSetDevice(db->device));
     Scratch &sc = scratch_for(db, db->stream);
     PIR_TRY(ensure_device(&sc.req, &sc.req_cap, (uint64_t)B * db->qpitch));
-    PIR_TRY(ensure_device(&sc.resp, &sc.resp_cap, (uint64_t)B * db->stride));
     // Host rows move in one contiguous copy each way (a pitched copy from or
     // to pageable memory goes row by row); pitches change on the device. Few
     // bytes go through mapped host memory instead, a kernel fetching the
@@ -882,27 +881,29 @@ static int read_sync(pir_db *db, const uint8_t *req_bits, uint32_t B, const uint
     // copies, each with a staging buffer and a wait of its own, made up half
     // of such a call's time (one request over 10 MiB 24 us, 38 with them).
     const uint64_t qb = db->qbytes, in_bytes = (uint64_t)B * qb, out_bytes = (uint64_t)B * db->bucket_bytes;
-    const uint64_t in_dev = ((uint64_t)B * db->qpitch + 15) & ~15ull;
+    const uint64_t in_dev = (uint64_t)B * db->qpitch;
     const bool q_mapped = db->io_host && in_dev <= HOST_IO;
     const bool q_direct = q_mapped || qb % 4 == 0, r_direct = db->stride == db->bucket_bytes;
-    if (!q_direct || !r_direct)
-        PIR_TRY(ensure_device(&sc.host_rows, &sc.host_rows_cap, std::max(q_direct ? 0 : in_bytes,
-                                                                           r_direct ? 0 : out_bytes)));
-    uint64_t qp = q_mapped ? db->qpitch : qb;
+    const uint64_t qp = q_direct && !q_mapped ? qb : db->qpitch;
+    const bool prep = use_prep(db, B);
+    const Plan p = prep ? Plan{} : choose_plan(db, B, qp);
+    const bool r_mapped = db->io_host && out_bytes <= HOST_IO && !prep && !seeds && writes_any_row(p);
+    const uint64_t rows = std::max(q_direct ? 0 : in_bytes, r_direct || r_mapped ? 0 : out_bytes);
+    if (rows)
+        PIR_TRY(ensure_device(&sc.host_rows, &sc.host_rows_cap, rows));
+    if (!r_mapped)
+        PIR_TRY(ensure_device(&sc.resp, &sc.resp_cap, (uint64_t)B * db->stride));
     if (q_mapped) {
-        uint8_t *rows = db->io_host;
         for (uint32_t r = 0; r < B; ++r) {
-            memcpy(rows + r * qp, req_bits + r * qb, qb);
-            memset(rows + r * qp + qb, 0, qp - qb);
+            memcpy(db->io_host + r * qp, req_bits + r * qb, qb);
+            memset(db->io_host + r * qp + qb, 0, qp - qb);
         }
-        PIR_TRY(ensure_device(&sc.req, &sc.req_cap, in_dev));
         HIP_TRY(launch_fetch(sc.req, db->io_map, in_dev, db->stream));
     } else if (q_direct) {
         HIP_TRY(hipMemcpyAsync(sc.req, req_bits, in_bytes, hipMemcpyHostToDevice, db->stream));
     } else {
         HIP_TRY(hipMemcpyAsync(sc.host_rows, req_bits, in_bytes, hipMemcpyHostToDevice, db->stream));
         HIP_TRY(hipMemcpy2DAsync(sc.req, db->qpitch, sc.host_rows, qb, qb, B, hipMemcpyDeviceToDevice, db->stream));
-        qp = db->qpitch;
     }
     ReadGeom g = read_geom(db, sc.req, qp, B, sc.resp, db->stride);
     if (seeds) {
@@ -912,16 +913,13 @@ static int read_sync(pir_db *db, const uint8_t *req_bits, uint32_t B, const uint
     }
     hipEvent_t eb, ee;
     PIR_TRY(profile_slot(db, &eb, &ee));
-    bool r_mapped = false;
-    if (use_prep(db, B)) {
+    if (prep) {
         LeafRead lr;
         PIR_TRY(prep_requests(db, sc, sc.req, qp, B, db->stream, &lr));
         PIR_TRY(prep_read(db, sc, lr, B, sc.resp, db->stride, g.keys, db->stream, eb, ee, nullptr));
     } else {
-        Plan p = choose_plan(db, B, qp);
         PIR_TRY(ensure_device(&sc.part, &sc.part_cap, partial_bytes(g, p)));
-        if (db->io_host && out_bytes <= HOST_IO && writes_any_row(p) && !g.keys) {
-            r_mapped = true;
+        if (r_mapped) {
             g.out = db->io_map + HOST_IO;
             g.out_pitch = g.out_bytes = db->bucket_bytes;
         }
@@ -971,37 +969,32 @@ static int read_async(pir_db *db, const void *d_req, uint64_t req_pitch, uint32_
     PIR_TRY(wait_published(db, s));
     const bool direct = !(reinterpret_cast<uintptr_t>(d_resp) & 15) && !(resp_pitch & 15) &&
                         db->stride == db->bucket_bytes;
+    const Plan p = prep ? Plan{} : choose_plan(db, B, qp);
+    // a split reduction writes answer rows at any alignment
+    const bool bytes = !direct && !prep && !d_keys && writes_any_row(p);
     void *out = d_resp;
     uint64_t op = resp_pitch;
-    if (!direct) {
+    if (!direct && !bytes) {
         PIR_TRY(ensure_device(&sc.resp, &sc.resp_cap, (uint64_t)B * db->stride));
         out = sc.resp;
         op = db->stride;
     }
     ReadGeom g = read_geom(db, q, qp, B, out, op);
     g.keys = static_cast<const uint32_t *>(d_keys);
+    if (bytes)
+        g.out_bytes = db->bucket_bytes;
     hipEvent_t eb, ee, done;
     PIR_TRY(profile_slot(db, &eb, &ee));
     PIR_TRY(reader_event(db, prep ? 2 : db->front, s, &done));
     if (prep) {
         PIR_TRY(prep_read(db, sc, lr, B, out, op, g.keys, s, eb, ee, direct ? done : nullptr));
     } else {
-        Plan p = choose_plan(db, B, qp);
         PIR_TRY(ensure_device(&sc.part, &sc.part_cap, partial_bytes(g, p)));
-        // a split reduction writes answer rows at any alignment
-        const bool bytes = !direct && writes_any_row(p) && !d_keys;
-        if (bytes) {
-            g.out = d_resp;
-            g.out_pitch = resp_pitch;
-            g.out_bytes = db->bucket_bytes;
-        }
         if (direct || bytes)
             g.done = done;  // the read's last kernel marks the end of its use of the snapshot
         HIP_TRY(launch_read(g, p, sc.part, s, eb, ee));
-        if (bytes)
-            return PIR_OK;
     }
-    if (direct)
+    if (direct || bytes)
         return PIR_OK;
     HIP_TRY(hipMemcpy2DAsync(d_resp, resp_pitch, sc.resp, db->stride, db->bucket_bytes, B,
                              hipMemcpyDeviceToDevice, s));

@@ -259,6 +259,24 @@ void stream_plans()
         }
 }
 
+// Answers that kernels write where they belong take no scratch: the calls
+// allocate the restaged requests and the splits' partial answers.
+void answer_scratch()
+{
+    const uint64_t n = 8200, row = 999, B = 40, restaged = B * 1040;
+    std::vector<uint8_t> q(B * 1026 + 1), out(B * 1001);
+    for (bool sync : {false, true}) {
+        Db db(n, 3, 333);
+        const pir_plan p = {PIR_KERNEL_MFMA, 64, 4, 4, 0};
+        CHECK(pir_set_plan(db.h, &p) == PIR_OK);
+        const uint64_t before = device_bytes;
+        CHECK((sync ? pir_read_batch(db.h, q.data(), B, out.data())
+                    : pir_read_batch_async(db.h, q.data() + 1, 1026, B, out.data() + 1, 1000, nullptr)) == PIR_OK);
+        CHECK(device_bytes - before == restaged + 4 * B * 1008);
+        CHECK(B * row <= out.size() && launched("xor_splits_kernel") >= 1);
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv)
@@ -269,6 +287,7 @@ int main(int argc, char **argv)
         {"code_without_pinned_memory", code_without_pinned_memory},
         {"tuned_leaves", tuned_leaves},
         {"stream_plans", stream_plans},
+        {"answer_scratch", answer_scratch},
     };
     const auto it = argc > 1 ? all.find(argv[1]) : all.end();
     if (it == all.end())

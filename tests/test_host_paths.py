@@ -25,7 +25,7 @@ def fake_hip(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["first_read", "read_without_pinned_memory", "code_without_pinned_memory",
-                                      "tuned_leaves", "stream_plans"])
+                                      "tuned_leaves", "stream_plans", "answer_scratch"])
 def test_host_paths(fake_hip, scenario):
     run = subprocess.run([fake_hip, scenario], capture_output=True, text=True, timeout=120)
     assert run.returncode == 0, run.stdout + run.stderr
