@@ -36,9 +36,39 @@ HBM_PEAK_GBS = 8000.0                      # MI355X HBM3E, published
 # 32-bit VALU lane-operations per second: 256 CUs x 128 lanes per clock x 2.4 GHz
 # = 78.6 T (the FP32 vector figure, 157.3 TFLOP/s, counts an FMA as two flops)
 VALU_PEAK_TOPS = 256 * 128 * 2.4e9 / 1e12
+# 4-bit products of the matrix cores per second: 256 CUs x 4 SIMDs x 2048 per
+# clock x 2.4 GHz = 5033 T (32 x 32 x 64 of them in 32 clocks of a SIMD)
+MFMA_PEAK_TOPS = 256 * 4 * 2048 * 2.4e9 / 1e12
 # LDS rates measured by the roofline probe (bytes per clock and CU, 16-byte
 # accesses, no bank conflicts), at 256 CUs and 2.4 GHz
 LDS_READ_BPC, LDS_WRITE_BPC = 204.9, 75.4
+
+
+def plain_roofline(alg_bytes: float, xor_ops: float, products: float | None, t_kernel: float, levels: int = 0):
+    """The roofline entry of a read's main kernel, which took t_kernel seconds:
+    against the memory rate when its algorithmic bytes take longest, else against
+    the units that do its work: the matrix cores for `products` (bits of request
+    times bits of database, None for other kernels), the VALU for the plain
+    method's XORs."""
+    t_hbm = alg_bytes / (HBM_PEAK_GBS * 1e9)
+    t_work = xor_ops / (VALU_PEAK_TOPS * 1e12) if products is None else products / (MFMA_PEAK_TOPS * 1e12)
+    if t_work < t_hbm:
+        return {"bound": "hbm", "achieved": round(alg_bytes / t_kernel / 1e9, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                "frac": round(t_hbm / t_kernel, 4), "traffic": None,
+                "achieved_is": "algorithmic bytes (database once, requests, answers) per second of the main "
+                               "read kernel"}
+    if products is not None:
+        return {"bound": "mfma", "achieved": round(products / t_kernel / 1e12, 3), "peak": round(MFMA_PEAK_TOPS, 2),
+                "unit": "TOP/s", "frac": round(t_work / t_kernel, 4), "traffic": None,
+                "achieved_is": "products of a request bit with a database bit, one 4-bit multiply-accumulate each, "
+                               "per second of the main read kernel"}
+    return {"bound": "alu", "achieved": round(xor_ops / t_kernel / 1e12, 3), "peak": round(VALU_PEAK_TOPS, 2),
+            "unit": "TOP/s", "frac": round(t_work / t_kernel, 4), "traffic": None,
+            "achieved_is": ("XORs of the plain method over the 7^L Strassen leaf products the kernel computes "
+                            "(one 32-bit XOR per selected leaf-bucket word) per second of the main read kernel"
+                            if levels else
+                            "XORs of the plain method (one 32-bit XOR per selected bucket word) per second "
+                            "of the main read kernel")}
 
 
 def lds_floor(plan, n: int, B: int, bucket_bytes: int):
@@ -127,12 +157,15 @@ KERNEL_NAMES = {1: "xorpir_tile_kernel", 2: "xorpir_tile_kernel", 3: "xorpir_m4r
                 4: "xorpir_m4rw_kernel", 5: "xorpir_mfma_kernel"}
 PLAN_PAIRS = 1 << 13
 PLAN_HALF_WAVES = 1 << 16
+PLAN_ONE_LAUNCH = 1 << 18
 
 
 def kernel_name(plan: dict) -> str:
     """Name of the main read kernel a plan launches."""
     if plan["kind"] == 4 and plan["flags"] & PLAN_PAIRS:
         return "xorpir_m4rh_kernel" if plan["flags"] & PLAN_HALF_WAVES else "xorpir_m4rp_kernel"
+    if plan["kind"] == 1 and plan["flags"] & PLAN_ONE_LAUNCH:
+        return "xorpir_small_kernel"
     return KERNEL_NAMES[plan["kind"]]
 
 
@@ -814,33 +847,23 @@ def fixed_bench(args, pir, torch, w, B: int, K: int, W: int, cpu_rows: int, cpu_
     hbm_achieved = alg_bytes / t_kernel / 1e9
     alu_achieved = xor_ops_alg / t_kernel / 1e12
     answers_tops = xor_ops / t_kernel / 1e12
-    t_hbm = alg_bytes / (HBM_PEAK_GBS * 1e9)
-    t_alu = xor_ops_alg / (VALU_PEAK_TOPS * 1e12)
-    if t_alu >= t_hbm:
-        roof = {"bound": "alu", "achieved": round(alu_achieved, 3), "peak": round(VALU_PEAK_TOPS, 2),
-                "unit": "TOP/s", "frac": round(alu_achieved / VALU_PEAK_TOPS, 4), "traffic": None,
-                "achieved_is": ("XORs of the plain method over the 7^L Strassen leaf products the kernel computes "
-                                "(one 32-bit XOR per selected leaf-bucket word) per second of the main read kernel"
-                                if args.prep else
-                                "XORs of the plain method (one 32-bit XOR per selected bucket word) per second "
-                                "of the main read kernel")}
-    else:
-        roof = {"bound": "hbm", "achieved": round(hbm_achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": round(hbm_achieved / HBM_PEAK_GBS, 4), "traffic": None,
-                "achieved_is": "algorithmic bytes (database once, requests, answers) per second of the main "
-                               "read kernel"}
+    leaves = 7 ** args.prep if args.prep else 1
+    unit = 32 << args.prep
+    nq, bq, cq = -(-w.n // unit) * unit >> args.prep, -(-B // (1 << args.prep)), w.bucket_bytes >> args.prep
+    # leaves take the tables unless the matrix cores are forced
+    products = None
+    if plan.kind == 5 and (args.kind or not args.prep):
+        products = leaves * nq * bq * 8 * cq if args.prep else w.n * B * 8 * w.bucket_bytes
+    roof = plain_roofline(alg_bytes, xor_ops_alg, products, t_kernel, args.prep)
     # With Strassen leaves the main kernel answers 7^L leaves (products of
     # n/2^L buckets x d*z/2^L bytes x B/2^L requests), in one launch when their
     # offsets are staged together (else one launch per leaf); its figures are
     # summed over the read's leaves and kern_ms spans the first leaf's start to
     # the last one's end.
-    leaves = 7 ** args.prep if args.prep else 1
     key = summary_key(w.name, args.prep)
     traffic = measured_traffic(key, plan)
     roof["traffic"] = traffic
     if args.prep:
-        unit = 32 << args.prep
-        nq, bq, cq = -(-w.n // unit) * unit >> args.prep, -(-B // (1 << args.prep)), w.bucket_bytes >> args.prep
         # the leaves take the automatic plan of their shape: the same family as
         # this batch's while both are above 256 requests
         one = lds_floor(plan, nq, bq, cq) if bq > 256 and B > 256 else None
