@@ -11,7 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libtalek_pir.so")
-PROBE = os.path.join(HERE, "roofline_probe")  # measured HBM, VALU and LDS peaks
+PROBE = os.path.join(HERE, "roofline_probe")  # measured HBM, VALU, LDS and matrix-core peaks
 ARCH = os.environ.get("TALEK_OFFLOAD_ARCH", "gfx950")
 
 SOURCES = [

@@ -8,6 +8,8 @@
 //     contiguous row slice (64 lanes x W dwords), so the accesses are free of
 //     bank conflicts; all indices stay inside the 64 KiB array. Reported per
 //     CU and clock at 2.4 GHz.
+//   * Matrix cores: products of 4-bit elements (32 x 32 x 64 an instruction),
+//     the operands in registers, half their elements zero and half one.
 //
 //   ./paper_2001_08250_amd/roofline_probe
 #include <hip/hip_runtime.h>
@@ -165,6 +167,59 @@ int run_valu(const char *what, uint32_t *d, int cus, int blocks_per_cu)
     return 0;
 }
 
+// CH accumulators per wave, in turn, each step a product of the same operands.
+template <int CH>
+__global__ __launch_bounds__(256) void mfma_chain(uint32_t *out, int iters)
+{
+    using i32x8 = int __attribute__((ext_vector_type(8)));
+    using f32x16 = float __attribute__((ext_vector_type(16)));
+    const uint32_t t = blockIdx.x * 256 + threadIdx.x;
+    i32x8 a = {}, b = {};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        a[k] = (int)(((t * 4 + k) * 2654435761u >> 3) & 0x11111111u);
+        b[k] = (int)(((t * 4 + k) * 2246822519u >> 2) & 0x11111111u);
+    }
+    f32x16 c[CH] = {};
+    for (int it = 0; it < iters; ++it) {
+#pragma unroll
+        for (int k = 0; k < CH; ++k)
+            c[k] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c[k], 4, 4, 0, 0, 0, 0);
+    }
+    float r = 0;
+#pragma unroll
+    for (int k = 0; k < CH; ++k)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            r += c[k][v];
+    out[t] = __builtin_bit_cast(uint32_t, r);
+}
+
+// Times it at `blocks_per_cu` workgroups of 4 waves per CU (one per SIMD each),
+// after as long an untimed launch: the clock takes milliseconds to settle.
+template <int CH>
+int run_mfma(const char *what, uint32_t *d, int cus, int blocks_per_cu)
+{
+    const int grid = cus * blocks_per_cu, iters = 200000;
+    hipEvent_t a, b;
+    if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&b) != hipSuccess)
+        return 1;
+    hipLaunchKernelGGL((mfma_chain<CH>), dim3(grid), dim3(256), 0, 0, d, iters);
+    (void)hipEventRecord(a, 0);
+    hipLaunchKernelGGL((mfma_chain<CH>), dim3(grid), dim3(256), 0, 0, d, iters);
+    (void)hipEventRecord(b, 0);
+    if (hipEventSynchronize(b) != hipSuccess)
+        return 1;
+    float ms = 0;
+    (void)hipEventElapsedTime(&ms, a, b);
+    const double products = (double)grid * 4 * iters * CH * 32 * 32 * 64;
+    printf("%-40s %2d waves/SIMD %7.1f T products/s %6.0f products/clk/SIMD\n", what, blocks_per_cu, products / ms / 1e9,
+           products / (ms * 1e-3) / cus / 4 / 2.4e9);
+    (void)hipEventDestroy(a);
+    (void)hipEventDestroy(b);
+    return 0;
+}
+
 template <int MODE, int W>
 int run(const char *what, uint32_t *d, int cus)
 {
@@ -232,6 +287,9 @@ int main()
     rc |= run_valu<16, false, 4>("v_xor_b32, 16 chains, unroll 4", d, cus, 8);
     for (int w : {1, 2, 4})
         rc |= run_valu<16, true, 4>("v_bitop3_b32, 16 chains, unroll 4", d, cus, w);
+    for (int w : {1, 2})
+        rc |= run_mfma<4>("4-bit matrix products, 4 accumulators", d, cus, w);
+    rc |= run_mfma<8>("4-bit matrix products, 8 accumulators", d, cus, 1);
     rc |= run<0, 1>("ds_read_b32 (4 B per lane)", d, p.multiProcessorCount);
     rc |= run<0, 2>("ds_read_b64 (8 B per lane)", d, p.multiProcessorCount);
     rc |= run<0, 4>("ds_read_b128 (16 B per lane)", d, p.multiProcessorCount);
