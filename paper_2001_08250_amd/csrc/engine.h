@@ -65,7 +65,7 @@ struct Plan {
     uint32_t tile;     // requests per wave
     uint32_t splits;   // bucket-range splits (1 = none)
     uint32_t unroll;   // buckets loaded ahead (M4R: waves per workgroup)
-    uint32_t flags;    // PLAN_SHARED_COLUMN
+    uint32_t flags;    // PLAN_* of the kind
 };
 constexpr uint32_t PLAN_SHARED_COLUMN = 1;
 constexpr uint32_t PLAN_ONE_LAUNCH = 1u << 18;  // whole bucket range per workgroup, no splits
@@ -81,8 +81,6 @@ constexpr uint32_t PLAN_PAIR_G6 = 1u << 17;
 // Device scratch the read needs for split partials: bytes.
 uint64_t partial_bytes(const ReadGeom &g, const Plan &p);
 
-// Fill in a complete plan (tile, splits, unroll) for geometry g from a
-// partial request (kind may be AUTO; zero fields mean "choose").
 // Whether p is the one-launch kernel's plan.
 inline bool one_launch(const Plan &p)
 {
@@ -91,6 +89,8 @@ inline bool one_launch(const Plan &p)
 }
 // Whether a read under p without keys writes answer rows at any alignment.
 inline bool writes_any_row(const Plan &p) { return p.splits > 1 || one_launch(p); }
+// Fill in a complete plan (tile, splits, unroll) for geometry g from a
+// partial request (kind may be AUTO; zero fields mean "choose").
 Plan resolve_plan(const ReadGeom &g, Plan want, int num_cus);
 // Bucket splits for one launch of `leaves` products of geometry g under plan p.
 uint32_t leaf_splits(const ReadGeom &g, const Plan &p, uint32_t leaves, int num_cus);

@@ -149,9 +149,11 @@ Plan resolve_plan(const ReadGeom &g, Plan want, int num_cus)
         // requests over 256 MiB of 256-byte rows, for 8 over 32 MiB of
         // 512-byte rows, and for one over 16 MiB of 64-byte rows). Above 8 the
         // matrix cores count the bits: they read D at its memory rate up to
-        // about 64 requests (24 / 64 requests over 1 GiB: 191 / 226 us against
-        // 275 / 307 with paired Four-Russians tables, 12 requests 194 against
-        // 222 masked) and need no tables, so small and narrow databases start
+        // about 64 requests (24 / 64 requests over 1 GiB: 191 / 230 us against
+        // 275 / 313 with paired Four-Russians tables, 12 requests 194 against
+        // 222 masked; 9 to 16 requests over 16 to 64 MiB would take 4 - 15%
+        // less with four waves of 4 masked, 21 - 24 against 25 us over 64 MiB,
+        // but more from 128 MiB on, 37 - 39 against 35) and need no tables, so small and narrow databases start
         // faster (256 requests over 4 MiB: 12 against 32 us). From about 160
         // requests per GiB on the tables, bound by the LDS, are as fast
         // (256 over 1 GiB: 684 against 691 us), and with 512 requests to a
@@ -210,8 +212,8 @@ Plan resolve_plan(const ReadGeom &g, Plan want, int num_cus)
             // over 1024 buckets 7.2 against 10.2 us, one over 4096 7.2 against
             // 9.5, 4 over 4096 10.8 against 10.6, 8 17 against 11, one over
             // 8192 of 4 KiB 11.6 against 10.0. Else a database that the caches
-            // hold (up to 64 MiB) is read by as many waves as there are; from 5 to 8 requests two
-            // waves of 4 share a 1 KiB column chunk, which halves the chain
+            // hold (up to 64 MiB) is read by as many waves as there are; from
+            // 5 to 8 requests two waves of 4 share a 1 KiB column chunk, which halves the chain
             // of scalar work per bucket (8 requests over 4 MiB 11.3 us, one
             // wave's tile of 8 13.3, over 64 MiB 19.7 and 20.5). A larger one
             // streams best from few places at a time: four waves per CU, each

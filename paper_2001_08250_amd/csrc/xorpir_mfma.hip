@@ -26,12 +26,16 @@
 //
 // What bounds it. With 32 and 64 requests to a workgroup the reading of D: 24
 // requests over 1 GiB 191 us (5.6 TB/s; 275 with paired Four-Russians tables),
-// 64 requests 226 (307). With 96 and 128 the products: the matrix cores make
-// 4.9e15 of them a second in a loop of nothing else, and about 3.5e15 here,
-// where staging takes issue slots (4 VALU operations fit beside a product),
-// every 16-byte LDS read holds the cores for about 10 clocks, and the clock
-// falls to 2.0 - 2.2 GHz under the load. 256 requests over 256 MiB: 163 us,
-// read 176 (192 with tables); 1000 over 1 GiB 2.55 ms (2.26 with tables).
+// 64 requests 230 (313), where the reading meets products that would take 190
+// by themselves: 5.1 VALU operations go with each of them. With 96 and 128 the
+// products: the matrix cores make 4.9e15 of them a second in a loop of nothing
+// else, and 2.9 - 3.3e15 here. 256 requests over 256 MiB: 165 - 170 us, read
+// 178 (192 with tables), of which the launch that reduces two splits takes 4
+// and the gap before it as much; the matrix cores are busy 64% of the cycles,
+// with 3.0 VALU operations to a product (4 fit beside one), and the wave of a
+// SIMD waits for the LDS, the barrier or memory in 15% of its cycles (a 16-byte
+// LDS read holds the cores for about 10 clocks); the clock falls to 1.9 - 2.3
+// GHz under the load. 1000 over 1 GiB 2.55 ms (2.26 with tables).
 // Eight waves of 128 accumulators took 167 us, and with the requests' operands
 // widened by every wave 172; 256 requests to a workgroup leave no registers
 // for the staging.
@@ -76,7 +80,6 @@ struct MfmaArgs {
     const uint8_t *D;
     uint64_t row_bytes;    // stride
     uint32_t stride4, stride16;
-    uint64_t n;
     uint64_t nblk;         // 32-bucket blocks of D, ceil(n / 32)
     uint64_t chunks;       // ceil(n / buckets per chunk)
     const uint32_t *Q;
@@ -84,7 +87,7 @@ struct MfmaArgs {
     uint32_t B;
     uint4 *out;
     uint64_t out_row16, out_split16;
-    uint32_t n_rt, slices, splits, tasks, tasks_per_xcd;
+    uint32_t n_rt, slices, tasks, tasks_per_xcd;
     uint64_t chunks_per_split;
 };
 
@@ -128,8 +131,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t chunk_of(const MfmaArgs &g, ui
 
 // A thread's share of a chunk: four columns of a quarter of the buckets of one
 // block, in G groups: row j of group e is bucket 4j + i, i = i0 + 2e (off: the
-// place of bucket i0). Blocks past the database read zero; their request bits
-// are zero too. ONCE: no other workgroup reads these rows and no cache keeps
+// place of bucket i0). Blocks past the database read zero, whatever request
+// bits they meet. ONCE: no other workgroup reads these rows and no cache keeps
 // them for the next read.
 template <bool ONCE>
 __device__ __forceinline__ u32x4 load_row(__amdgpu_buffer_rsrc_t rows, uint32_t off, uint32_t at)
@@ -582,7 +585,6 @@ hipError_t launch_mfma_read(const ReadGeom &g, const Plan &p, void *partials, hi
     a.row_bytes = g.stride;
     a.stride16 = (uint32_t)(g.stride / 16);
     a.stride4 = a.stride16 * 4;
-    a.n = g.n;
     a.nblk = (g.n + 31) / 32;
     a.chunks = mfma_chunks(g.n, p);
     a.Q = static_cast<const uint32_t *>(g.Q);
@@ -590,7 +592,6 @@ hipError_t launch_mfma_read(const ReadGeom &g, const Plan &p, void *partials, hi
     a.B = g.B;
     a.n_rt = (g.B + p.tile - 1) / p.tile;
     a.slices = (a.stride4 + s.cw - 1) / s.cw;
-    a.splits = p.splits;
     a.chunks_per_split = (a.chunks + p.splits - 1) / p.splits;
     if (p.splits > 1) {
         a.out = static_cast<uint4 *>(partials);
@@ -601,12 +602,13 @@ hipError_t launch_mfma_read(const ReadGeom &g, const Plan &p, void *partials, hi
         a.out_row16 = g.out_pitch / 16;
         a.out_split16 = 0;
     }
-    const uint64_t tasks = (uint64_t)a.n_rt * a.slices * a.splits;
+    const uint64_t tasks = (uint64_t)a.n_rt * a.slices * p.splits;
     if ((tasks + 7) / 8 * 8 * THREADS > 0xffffffffull)  // a launch holds fewer than 2^32 work-items
         return hipErrorInvalidValue;
     a.tasks = (uint32_t)tasks;
     a.tasks_per_xcd = (uint32_t)((tasks + 7) / 8);
-    hipExtLaunchKernelGGL(s.fn[a.n_rt == 1 && g.n * g.stride > CACHED_BYTES], dim3(a.tasks_per_xcd * 8), dim3(THREADS), 0, stream, eb, ee, 0, a);
+    const bool once = a.n_rt == 1 && g.n * g.stride > CACHED_BYTES;
+    hipExtLaunchKernelGGL(s.fn[once], dim3(a.tasks_per_xcd * 8), dim3(THREADS), 0, stream, eb, ee, 0, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.splits <= 1)
         return e;

@@ -30,8 +30,9 @@
 // memory rows open, so a large database is read by four waves per CU with 8
 // rows each in flight and, where no cache keeps it, by nontemporal loads (one
 // request over 1 GiB 158 us, 6.8 TB/s, 8 requests 161; 32 waves per CU with
-// plain loads 202, 8 waves 194). Small databases take two launches' time
-// (8 requests over 4 MiB 11.5 us).
+// plain loads 202, 8 waves 194). Small databases take their launches' time: one
+// where a kernel of their own answers without splits (8 requests over 4 MiB
+// 7.2 us), else two (11.5 us).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -88,7 +89,9 @@ __device__ __forceinline__ void apply_bucket(uint4 (&acc)[T], const uint4 v, con
 }
 
 // 16 bytes of D; ONCE: no other request tile reads them and no cache keeps them
-// for the next read.
+// for the next read. (SKIP over 1 GiB, 1 to 16 requests: 160 - 224 us with
+// nontemporal loads where plain ones take 187 - 250, level where its branches
+// take longest.)
 template <bool ONCE>
 __device__ __forceinline__ uint4 load_d(const uint8_t *p)
 {
@@ -309,11 +312,11 @@ __global__ __launch_bounds__(SMALL_WG) void xorpir_small_kernel(const TileArgs a
 // resp[r][c] = XOR over s of partials[s][r][c]. A workgroup covers TI
 // consecutive 16-byte words; its WG / TI thread groups take every
 // (WG / TI)-th split from their own first one and combine their sums in LDS.
-// row_bytes > 0: rows of that many bytes at any address (out, out_pitch);
-// writing them here saves such a read a copy of its answers (24 requests for
-// 999-byte buckets 22.4 us, 24.6 with it).
 // Few words and many splits (a batch of one request split over every bucket
-// range) thus still spread the partials over many threads.
+// range) thus still spread the partials over many threads. row_bytes > 0: rows
+// of that many bytes at any address (out, out_pitch); writing them here saves
+// such a read a copy of its answers (24 requests for 999-byte buckets 22.4 us,
+// 24.6 with it).
 template <int TI>
 __global__ __launch_bounds__(WG) void xor_splits_kernel(const uint4 *__restrict__ P, uint64_t split16,
                                                         uint32_t splits, uint64_t count, uint32_t stride16,
